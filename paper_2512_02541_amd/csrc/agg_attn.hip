@@ -5,8 +5,9 @@
 // same kernel is ordinary global attention (Sec. 4.2).
 //
 // Mapping to gfx950
-//   * One workgroup = 4 wavefronts; a wavefront owns kQB blocks of 32 queries for the
-//     whole key loop and keeps Q and the output accumulator in registers.
+//   * One workgroup = 4 wavefronts; a wavefront owns kQB blocks of 16 kJ queries (2 x 32 at full
+//     width) for the whole key loop and keeps Q and the output accumulator in registers.  The
+//     last workgroups of a launch may be narrower (plan_tiles).
 //   * Both products run on v_mfma_f32_16x16x32_bf16, which accumulates 32 products per pass
 //     through its four accumulator registers: half the accumulator traffic per flop of the
 //     32x32x16 shape, and the part is power-limited on this kernel (measured on hashed
@@ -32,7 +33,7 @@
 //     addresses.
 //   * At head dimension 64 the vector ALU is as loaded as the matrix core (one
 //     exponential per 256 MFMA flops) and a wavefront issues in order, so the key
-//     loop is a software pipeline over "units" (32 keys x 32 queries).  Step u
+//     loop is a software pipeline over "units" (32 keys x 16 kJ queries).  Step u
 //     exponentiates unit u on the vector ALU while the matrix core computes the
 //     scores of unit u + kQB - 1 and then P V of unit u - 1.  K fragments of a
 //     32-key block are fetched from LDS once per kQB units, V fragments likewise.
@@ -69,20 +70,17 @@ typedef float f32x2 __attribute__((ext_vector_type(2)));
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
 
-#ifndef AGG_QB
-#define AGG_QB 2
-#endif
-#ifndef AGG_WAVES
-#define AGG_WAVES 4
-#endif
-
-constexpr int kQB = AGG_QB;             // 32-query blocks per wavefront
-constexpr int kWaves = AGG_WAVES;       // wavefronts per workgroup
+constexpr int kWaves = 4;               // wavefronts per workgroup
 constexpr int kAttnThreads = 64 * kWaves;
-constexpr int kWaveQ = 32 * kQB;        // queries per wavefront
-constexpr int kQTile = kWaves * kWaveQ; // queries per workgroup
-constexpr int kBlocksPerCu = 8 / (kWaves * (kQB == 2 ? 1 : 2));  // two wavefronts per SIMD at kQB = 2
+constexpr int kBlocksPerCu = 2;         // two wavefronts per SIMD
 constexpr int kXcds = 8;
+constexpr int kCus = 256;
+
+// How many queries a wavefront owns: kQB blocks (the units of the key loop's pipeline) of kJ
+// tiles of 16.  The full width is kQB = kJ = 2; narrower workgroups finish a launch (see
+// plan_tiles).
+constexpr int wave_queries(int qb, int j) { return 16 * qb * j; }
+constexpr int kQTile = kWaves * wave_queries(2, 2);  // queries of a full-width workgroup (256)
 constexpr int kLdsTiles = 3;
 constexpr int kEpiStride = kHeadDim + 8;  // bf16 per query row of the epilogue's LDS tile (padded)
 constexpr int kChunks = kTileElems / 8;  // 16-byte chunks per K or V tile (512)
@@ -175,63 +173,66 @@ __device__ __forceinline__ float quad_max(float x) {
 }
 
 // zero-padded rows of the last tile: key index inside the tile >= valid -> -inf
-__device__ __forceinline__ void mask_unit(f32x4 (&S)[4], int kb, int valid, int G) {
+template <int kJ>
+__device__ __forceinline__ void mask_unit(f32x4 (&S)[2 * kJ], int kb, int valid, int G) {
 #pragma unroll
   for (int kt = 0; kt < 2; ++kt)
 #pragma unroll
     for (int r = 0; r < 4; ++r) {
       const int km = 32 * kb + 8 * kt + row_key(4 * G + r);
       if (km >= valid) {
-        S[2 * kt][r] = -INFINITY;
-        S[2 * kt + 1][r] = -INFINITY;
+#pragma unroll
+        for (int j = 0; j < kJ; ++j) S[kJ * kt + j][r] = -INFINITY;
       }
     }
 }
 
-// Everything a wavefront keeps in registers across the key loop.  qb = 32-query block, j = its
+// Everything a wavefront keeps in registers across the key loop.  qb = query block, j = its
 // 16-query tile, kt = 16-key tile of a key block, h = half of the channel range, dt = 16-channel
 // tile of the output.
+template <int kQB, int kJ>
 struct Wave {
-  Frag Qf[kQB][4];      // [qb][2 j + h]: B operand of S^T = K Q^T, pre-multiplied by scale*log2(e)
-  f32x4 O[kQB][2][4];   // [qb][j][dt]: O^T accumulator; channel = 16 dt + 4 G + r, query = c
-  f32x4 S[kQB][4];      // [qb][2 kt + j]: score tiles in flight; key = row_key(4 G + r) + 8 kt
-  f32x4 L[kQB][2];      // [qb][j]: fast path: the whole row sum, kept by the matrix core (four equal copies)
-  float la[kQB][2];     // [qb][j]: general path: this lane's part of the row sum
-  float mref[kQB][2];   // general path: the row's reference (base-2 logit)
-  Frag a[4];            // [2 kt + h]: K fragments of the block whose scores are being computed
-  Frag v[4];            // [dt]: V fragments of the block whose P V is being accumulated
-  Frag P[2];            // [j]: probabilities of the previous unit
+  Frag Qf[kQB][2 * kJ];    // [qb][2 j + h]: B operand of S^T = K Q^T, pre-multiplied by scale*log2(e)
+  f32x4 O[kQB][kJ][4];     // [qb][j][dt]: O^T accumulator; channel = 16 dt + 4 G + r, query = c
+  f32x4 S[kQB][2 * kJ];    // [qb][kJ kt + j]: score tiles in flight; key = row_key(4 G + r) + 8 kt
+  f32x4 L[kQB][kJ];        // [qb][j]: fast path: the whole row sum, kept by the matrix core (four equal copies)
+  float la[kQB][kJ];       // [qb][j]: general path: this lane's part of the row sum
+  float mref[kQB][kJ];     // general path: the row's reference (base-2 logit)
+  Frag a[4];               // [2 kt + h]: K fragments of the block whose scores are being computed
+  Frag v[4];               // [dt]: V fragments of the block whose P V is being accumulated
+  Frag P[kJ];              // [j]: probabilities of the previous unit
 };
 
-// Probabilities of the 16 base-2 logits a lane holds for a unit, packed as the B operands of
+// Probabilities of the 8 kJ base-2 logits a lane holds for a unit, packed as the B operands of
 // the PV MFMAs: for query tile j, contraction elements 8 G .. 8 G + 7 are key tile 0's rows, then
-// key tile 1's.  The two query tiles alternate in the instruction stream.
-__device__ __forceinline__ void exp_unit(const f32x4 (&S)[4], Frag (&P)[2]) {
+// key tile 1's.  The query tiles alternate in the instruction stream.
+template <int kJ>
+__device__ __forceinline__ void exp_unit(const f32x4 (&S)[2 * kJ], Frag (&P)[kJ]) {
 #pragma unroll
   for (int kt = 0; kt < 2; ++kt)
 #pragma unroll
     for (int i = 0; i < 2; ++i)
 #pragma unroll
-      for (int j = 0; j < 2; ++j)
-        P[j].u[2 * kt + i] = pack_bf16(fast_exp2(S[2 * kt + j][2 * i]), fast_exp2(S[2 * kt + j][2 * i + 1]));
+      for (int j = 0; j < kJ; ++j)
+        P[j].u[2 * kt + i] = pack_bf16(fast_exp2(S[kJ * kt + j][2 * i]), fast_exp2(S[kJ * kt + j][2 * i + 1]));
 }
 
 // General path: the same, and the sums of each query tile's part (there the vector ALU keeps
 // the sums: the unit's own sum is what tells that a score has run away from the row's reference,
 // and it is needed before the probabilities reach the matrix core)
-__device__ __forceinline__ void exp_unit_sum(const f32x4 (&S)[4], Frag (&P)[2], float& l0, float& l1) {
+template <int kJ>
+__device__ __forceinline__ void exp_unit_sum(const f32x4 (&S)[2 * kJ], Frag (&P)[kJ], float (&l)[kJ]) {
 #pragma unroll
   for (int kt = 0; kt < 2; ++kt)
 #pragma unroll
     for (int i = 0; i < 2; ++i)
 #pragma unroll
-      for (int j = 0; j < 2; ++j) {
-        float& l = j ? l1 : l0;
-        const float e0 = fast_exp2(S[2 * kt + j][2 * i]);
-        const float e1 = fast_exp2(S[2 * kt + j][2 * i + 1]);
+      for (int j = 0; j < kJ; ++j) {
+        const float e0 = fast_exp2(S[kJ * kt + j][2 * i]);
+        const float e1 = fast_exp2(S[kJ * kt + j][2 * i + 1]);
         P[j].u[2 * kt + i] = pack_bf16(e0, e1);
-        l += e0;
-        l += e1;
+        l[j] += e0;
+        l[j] += e1;
       }
 }
 
@@ -444,49 +445,49 @@ struct TileCopier {
   }
 };
 
-// Scores of one unit: the 32 keys of block fragments `a` against the 32 queries of block tq.
+// Scores of one unit: the 32 keys of block fragments `a` against the 16 kJ queries of block tq.
 // General path: the accumulator starts at minus the row's reference instead of zero, so the
 // scores come out relative to it at no cost (the reference is a float, nothing is split).
-template <bool kGen>
-__device__ __forceinline__ void score_unit(const Wave& w, int tq, f32x4 (&Sn)[4]) {
-  f32x4 init[2];
+template <bool kGen, int kQB, int kJ>
+__device__ __forceinline__ void score_unit(const Wave<kQB, kJ>& w, int tq, f32x4 (&Sn)[2 * kJ]) {
+  f32x4 init[kJ];
 #pragma unroll
-  for (int j = 0; j < 2; ++j) {
+  for (int j = 0; j < kJ; ++j) {
     const float m = kGen ? -w.mref[tq][j] : 0.f;
     init[j] = f32x4{m, m, m, m};
   }
 #pragma unroll
   for (int kt = 0; kt < 2; ++kt)
 #pragma unroll
-    for (int j = 0; j < 2; ++j) Sn[2 * kt + j] = AGG_MFMA16(w.a[2 * kt], w.Qf[tq][2 * j], init[j]);
+    for (int j = 0; j < kJ; ++j) Sn[kJ * kt + j] = AGG_MFMA16(w.a[2 * kt], w.Qf[tq][2 * j], init[j]);
 #pragma unroll
   for (int kt = 0; kt < 2; ++kt)
 #pragma unroll
-    for (int j = 0; j < 2; ++j)
-      Sn[2 * kt + j] = AGG_MFMA16(w.a[2 * kt + 1], w.Qf[tq][2 * j + 1], Sn[2 * kt + j]);
+    for (int j = 0; j < kJ; ++j)
+      Sn[kJ * kt + j] = AGG_MFMA16(w.a[2 * kt + 1], w.Qf[tq][2 * j + 1], Sn[kJ * kt + j]);
 }
 // O^T += V^T P^T for the unit whose probabilities are in w.P.  Fast path: the row sums are one
 // more product, a row of ones against P^T: every row of that 16 x 16 result is the sum of the
 // unit's 32 probabilities of a query, so each lane keeps the whole sum and the vector ALU adds
 // nothing.
-template <bool kGen>
-__device__ __forceinline__ void pv_unit(Wave& w, int pq) {
+template <bool kGen, int kQB, int kJ>
+__device__ __forceinline__ void pv_unit(Wave<kQB, kJ>& w, int pq) {
 #pragma unroll
   for (int dt = 0; dt < 4; ++dt)
 #pragma unroll
-    for (int j = 0; j < 2; ++j) w.O[pq][j][dt] = AGG_MFMA16(w.v[dt], w.P[j], w.O[pq][j][dt]);
+    for (int j = 0; j < kJ; ++j) w.O[pq][j][dt] = AGG_MFMA16(w.v[dt], w.P[j], w.O[pq][j][dt]);
   if (!kGen) {
     Frag ones;
     ones.u = u32x4{0x3F803F80u, 0x3F803F80u, 0x3F803F80u, 0x3F803F80u};
 #pragma unroll
-    for (int j = 0; j < 2; ++j) w.L[pq][j] = AGG_MFMA16(ones, w.P[j], w.L[pq][j]);
+    for (int j = 0; j < kJ; ++j) w.L[pq][j] = AGG_MFMA16(ones, w.P[j], w.L[pq][j]);
   }
 }
 
 // One step of the pipeline inside tile `cur` (see the file header).  kLast: the tile is the
 // last one (`valid` of its 64 rows exist, nothing follows).  kGen: general path.
-template <int kSrc, bool kLast, bool kGen>
-__device__ __forceinline__ void tile_steps(Wave& w, const u32x4* __restrict__ lds, int cur, int nxt,
+template <int kSrc, bool kLast, bool kGen, int kQB, int kJ>
+__device__ __forceinline__ void tile_steps(Wave<kQB, kJ>& w, const u32x4* __restrict__ lds, int cur, int nxt,
                                            int valid, const FragAddr& fa, int G) {
 #pragma unroll
   for (int sg = 0; sg < 2 * kQB; ++sg) {
@@ -498,45 +499,47 @@ __device__ __forceinline__ void tile_steps(Wave& w, const u32x4* __restrict__ ld
 
     // ---- matrix core, part 1: scores of unit `un` ----
     const bool do_qk = !(kLast && beyond);
-    f32x4 Sn[4];
-    if (do_qk) score_unit<kGen>(w, tq, Sn);
+    f32x4 Sn[2 * kJ];
+    if (do_qk) score_unit<kGen, kQB, kJ>(w, tq, Sn);
     if (tq == kQB - 1) {  // that was the block's last unit: fragments of the following block
       if (un / kQB == 0) load_k_frags<kSrc>(lds, cur, 1, fa, w.a);
       else if (!kLast) load_k_frags<kSrc>(lds, nxt, 0, fa, w.a);
     }
 
     // ---- vector ALU: probabilities of unit sg ----
-    Frag Pn[2];
-    float u0 = 0.f, u1 = 0.f;  // general path: the unit's own row sums
+    Frag Pn[kJ];
+    float unit_sum[kJ];  // general path: the unit's own row sums
+#pragma unroll
+    for (int j = 0; j < kJ; ++j) unit_sum[j] = 0.f;
     {
-      f32x4 (&S)[4] = w.S[qb];
-      if (kLast && valid < kTileRows) mask_unit(S, kb, valid, G);
+      f32x4 (&S)[2 * kJ] = w.S[qb];
+      if (kLast && valid < kTileRows) mask_unit<kJ>(S, kb, valid, G);
       if (!kGen) {
-        exp_unit(S, Pn);
+        exp_unit<kJ>(S, Pn);
       } else {
         // the scores are already relative to the row's reference; whether it still holds is
         // looked at below, behind the step's last MFMA
-        exp_unit_sum(S, Pn, u0, u1);
+        exp_unit_sum<kJ>(S, Pn, unit_sum);
       }
     }
     if (do_qk) {
 #pragma unroll
-      for (int i = 0; i < 4; ++i) w.S[tq][i] = Sn[i];
+      for (int i = 0; i < 2 * kJ; ++i) w.S[tq][i] = Sn[i];
     }
 
     // ---- matrix core, part 2: P V of unit sg - 1 ----
-    pv_unit<kGen>(w, pq);
+    pv_unit<kGen, kQB, kJ>(w, pq);
     if (qb == 0) load_v_frags<kSrc>(lds, cur, kb, fa, w.v);  // the previous block is done with them
-    w.P[0] = Pn[0];
-    w.P[1] = Pn[1];
+#pragma unroll
+    for (int j = 0; j < kJ; ++j) w.P[j] = Pn[j];
     // Issue order inside the step: MFMAs and exponentials alternate one by one, a conversion
     // after every second pair (general path: pairs of MFMAs, then their share of the vector work,
     // which there includes the additions).  Left to itself the scheduler bunches the MFMAs, and
     // the wavefront then stalls on the matrix pipe with vector work still to issue.
     if (!kGen) {
-      __builtin_amdgcn_sched_group_barrier(0x008, 2, 0);  // the row-sum products of the last unit
+      __builtin_amdgcn_sched_group_barrier(0x008, kJ, 0);  // the row-sum products of the last unit
 #pragma unroll
-      for (int i = 0; i < 8; ++i) {
+      for (int i = 0; i < 4 * kJ; ++i) {
         __builtin_amdgcn_sched_group_barrier(0x400, 1, 0);  // transcendental
         __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);  // MFMA
         __builtin_amdgcn_sched_group_barrier(0x400, 1, 0);
@@ -545,7 +548,7 @@ __device__ __forceinline__ void tile_steps(Wave& w, const u32x4* __restrict__ ld
       }
     } else {
 #pragma unroll
-      for (int i = 0; i < 8; ++i) {
+      for (int i = 0; i < 4 * kJ; ++i) {
         __builtin_amdgcn_sched_group_barrier(0x008, 2, 0);
         __builtin_amdgcn_sched_group_barrier(0x400, 2, 0);
         __builtin_amdgcn_sched_group_barrier(0x002, 3, 0);  // conversion and two additions
@@ -557,15 +560,18 @@ __device__ __forceinline__ void tile_steps(Wave& w, const u32x4* __restrict__ ld
       // cannot hide in them.  Rare, wavefront-uniform: raise the reference of the rows that need
       // it (the others keep theirs: shift 0, factor 1), scale what they have accumulated, and
       // redo the unit's probabilities (its scores are untouched until the next step).
-      if (__builtin_amdgcn_ballot_w64(!(u0 + u1 < kUnitHi)) != 0) {
-        f32x4 (&S)[4] = w.S[qb];
+      float all = unit_sum[0];
 #pragma unroll
-        for (int j = 0; j < 2; ++j) {
+      for (int j = 1; j < kJ; ++j) all += unit_sum[j];
+      if (__builtin_amdgcn_ballot_w64(!(all < kUnitHi)) != 0) {
+        f32x4 (&S)[2 * kJ] = w.S[qb];
+#pragma unroll
+        for (int j = 0; j < kJ; ++j) {
           float mx = S[j][0];
 #pragma unroll
           for (int kt = 0; kt < 2; ++kt)
 #pragma unroll
-            for (int r = 0; r < 4; ++r) mx = fmaxf(mx, S[2 * kt + j][r]);
+            for (int r = 0; r < 4; ++r) mx = fmaxf(mx, S[kJ * kt + j][r]);
           mx = quad_max(mx);  // the four lanes of a row agree
           const float old = w.mref[qb][j];
           if (mx > kLazy) w.mref[qb][j] = old + mx;
@@ -574,19 +580,19 @@ __device__ __forceinline__ void tile_steps(Wave& w, const u32x4* __restrict__ ld
 #pragma unroll
           for (int kt = 0; kt < 2; ++kt)
 #pragma unroll
-            for (int r = 0; r < 4; ++r) S[2 * kt + j][r] -= d;
+            for (int r = 0; r < 4; ++r) S[kJ * kt + j][r] -= d;
 #pragma unroll
           for (int dt = 0; dt < 4; ++dt)
 #pragma unroll
             for (int r = 0; r < 4; ++r) w.O[qb][j][dt][r] *= f;
           w.la[qb][j] *= f;
         }
-        u0 = 0.f;
-        u1 = 0.f;
-        exp_unit_sum(S, w.P, u0, u1);
+#pragma unroll
+        for (int j = 0; j < kJ; ++j) unit_sum[j] = 0.f;
+        exp_unit_sum<kJ>(S, w.P, unit_sum);
       }
-      w.la[qb][0] += u0;
-      w.la[qb][1] += u1;
+#pragma unroll
+      for (int j = 0; j < kJ; ++j) w.la[qb][j] += unit_sum[j];
     }
   }
 }
@@ -594,8 +600,8 @@ __device__ __forceinline__ void tile_steps(Wave& w, const u32x4* __restrict__ ld
 // The key loop of one path.  `first_tile` runs once tile 0 is resident and its first K fragments
 // are loaded (the general path takes its reference there).  Returns false when the fast path
 // found a row sum it cannot trust.
-template <int kSrc, bool kGen, class FirstTile>
-__device__ __forceinline__ bool key_loop(Wave& w, u32x4* __restrict__ lds, const KvSource& src,
+template <int kSrc, bool kGen, int kQB, int kJ, class FirstTile>
+__device__ __forceinline__ bool key_loop(Wave<kQB, kJ>& w, u32x4* __restrict__ lds, const KvSource& src,
                                          int ntiles, int last_valid, int tid, int wave,
                                          const FragAddr& fa, int G, FirstTile&& first_tile) {
   TileCopier<kSrc> copy;
@@ -610,10 +616,10 @@ __device__ __forceinline__ bool key_loop(Wave& w, u32x4* __restrict__ lds, const
   first_tile();
 #pragma unroll
   for (int i = 0; i < 4; ++i) w.v[i].u = u32x4{0u, 0u, 0u, 0u};
-  w.P[0].u = u32x4{0u, 0u, 0u, 0u};
-  w.P[1].u = u32x4{0u, 0u, 0u, 0u};
 #pragma unroll
-  for (int qb = 0; qb + 1 < kQB; ++qb) score_unit<kGen>(w, qb, w.S[qb]);
+  for (int j = 0; j < kJ; ++j) w.P[j].u = u32x4{0u, 0u, 0u, 0u};
+#pragma unroll
+  for (int qb = 0; qb + 1 < kQB; ++qb) score_unit<kGen, kQB, kJ>(w, qb, w.S[qb]);
 
   int t = 0, cur = 0;
   bool ok = true;
@@ -625,7 +631,7 @@ __device__ __forceinline__ bool key_loop(Wave& w, u32x4* __restrict__ lds, const
     break;                                                                                  \
   }                                                                                         \
   if (t + 2 < ntiles) copy.issue((CUR + 2) % kLdsTiles);                                    \
-  tile_steps<kSrc, false, kGen>(w, lds, CUR, (CUR + 1) % kLdsTiles, kTileRows, fa, G);      \
+  tile_steps<kSrc, false, kGen, kQB, kJ>(w, lds, CUR, (CUR + 1) % kLdsTiles, kTileRows, fa, G);      \
   wait_vm0();                                                                               \
   lds_barrier();                                                                            \
   ++t;
@@ -637,7 +643,8 @@ __device__ __forceinline__ bool key_loop(Wave& w, u32x4* __restrict__ lds, const
       bool bad = false;
 #pragma unroll
       for (int qb = 0; qb < kQB; ++qb)
-        bad = bad || !(w.L[qb][0][0] < kSumHi) || !(w.L[qb][1][0] < kSumHi);
+#pragma unroll
+        for (int j = 0; j < kJ; ++j) bad = bad || !(w.L[qb][j][0] < kSumHi);
       if (__syncthreads_or(bad ? 1 : 0)) {
         ok = false;
         break;
@@ -646,10 +653,17 @@ __device__ __forceinline__ bool key_loop(Wave& w, u32x4* __restrict__ lds, const
   }
   if (!ok) return false;
   // last tile (runtime buffer number), then the P V of its last unit
-  tile_steps<kSrc, true, kGen>(w, lds, cur, 0, last_valid, fa, G);
-  pv_unit<kGen>(w, kQB - 1);
+  tile_steps<kSrc, true, kGen, kQB, kJ>(w, lds, cur, 0, last_valid, fa, G);
+  pv_unit<kGen, kQB, kJ>(w, kQB - 1);
   return true;
 }
+
+// How a pair's queries are cut: n_full workgroups of kQTile queries, then n_tail of tail_q.
+// The launch order is one list of all tiles, pair by pair (tails_last 0), or all full tiles and
+// then all tails (1).
+struct TilePlan {
+  int n_full, n_tail, tail_q, tails_last;
+};
 
 // Kernel arguments.
 struct AttnArgs {
@@ -660,7 +674,8 @@ struct AttnArgs {
   const float *kmean, *vmean;
   uint16_t* O;
   float* lse;
-  int nqt, npairs;
+  int npairs;
+  TilePlan plan;
   const uint32_t* kept_bits;
   const int32_t* nd_dev;
   const int32_t* list;   // kSrcIndexed: token ids of the keys, [list_stride] per batch element
@@ -669,10 +684,13 @@ struct AttnArgs {
 
 __shared__ __align__(16) uint16_t smem[2 * kLdsTiles * kTileElems];  // K tiles, then V tiles
 
-// One workgroup's rows by one of the two paths.  Returns false, without storing anything, when
-// the fast path met a row it cannot handle.
-template <int kSrc, bool kGen>
-__device__ __forceinline__ bool attend(const AttnArgs& p, int b, int h, int qt) {
+// One workgroup's queries q_begin .. q_end - 1 (at most what its wavefronts hold) by one of the
+// two paths.  Returns false, without storing anything, when the fast path met a row it cannot
+// handle.
+template <int kSrc, bool kGen, int kQB, int kJ>
+__device__ __forceinline__ bool attend(const AttnArgs& p, int b, int h, int64_t q_begin,
+                                       int64_t q_end) {
+  constexpr int kWaveQ = wave_queries(kQB, kJ);
   const Geom& g = p.g;
   u32x4* lds = reinterpret_cast<u32x4*>(smem);
   const int tid = threadIdx.x;
@@ -700,19 +718,19 @@ __device__ __forceinline__ bool attend(const AttnArgs& p, int b, int h, int qt) 
     src.list = kSrc == kSrcIndexed ? p.list + (int64_t)b * p.list_stride : nullptr;
   }
 
-  Wave w;
-  bool dropped[kQB][2];
-  float l_self[kQB][2], l_mean[kQB][2];  // base-2 logits of the extras (-inf when absent)
+  Wave<kQB, kJ> w;
+  bool dropped[kQB][kJ];
+  float l_self[kQB][kJ], l_mean[kQB][kJ];  // base-2 logits of the extras (-inf when absent)
   // caller's list: membership comes from a bitmap, the dropped count from device memory
   const int64_t n_drop = p.nd_dev ? (int64_t)p.nd_dev[b] : g.n_dropped;
   const bool use_mean = (p.flags & AGG_MEAN) && n_drop > 0;
   const bool use_diag = (p.flags & AGG_DIAG) && (p.kept_bits != nullptr || n_drop > 0);
   const uint32_t* kbits = p.kept_bits ? p.kept_bits + (int64_t)b * ((g.NQ + 31) / 32) : nullptr;
-  const int64_t q_wave = (int64_t)qt * kQTile + wave * kWaveQ;
+  const int64_t q_wave = q_begin + wave * kWaveQ;
   // first element of query (qb, j, c)'s row of this head in Q, K, V and O
   auto row_base = [&](int qb, int j) {
-    const int64_t q = q_wave + qb * 32 + j * 16 + c;
-    const int64_t qc = q < g.NQ ? q : g.NQ - 1;  // tail rows recompute the last query, never stored
+    const int64_t q = q_wave + (qb * kJ + j) * 16 + c;
+    const int64_t qc = q < q_end ? q : q_end - 1;  // tail rows recompute the last query, never stored
     return (((int64_t)b * g.NQ + qc) * g.H + h) * kHeadDim;
   };
 
@@ -722,8 +740,8 @@ __device__ __forceinline__ bool attend(const AttnArgs& p, int b, int h, int qt) 
 #pragma unroll
   for (int qb = 0; qb < kQB; ++qb)
 #pragma unroll
-    for (int j = 0; j < 2; ++j) {
-      const int64_t q = q_wave + qb * 32 + j * 16 + c;
+    for (int j = 0; j < kJ; ++j) {
+      const int64_t q = q_wave + (qb * kJ + j) * 16 + c;
       const int64_t qbase = row_base(qb, j);
 #pragma unroll
       for (int hh = 0; hh < 2; ++hh) {
@@ -734,7 +752,7 @@ __device__ __forceinline__ bool attend(const AttnArgs& p, int b, int h, int qt) 
               pack_bf16(bf16_lo(raw[i]) * p.qscale, bf16_hi(raw[i]) * p.qscale);
       }
       dropped[qb][j] =
-          use_diag && q < g.NQ &&
+          use_diag && q < q_end &&
           (kbits ? ((kbits[q >> 5] >> (q & 31)) & 1u) == 0u : (bool)token_is_dropped(g, q));
       float dot_self = 0.f, dot_mean = 0.f;
       if (use_mean || use_diag) {
@@ -800,7 +818,7 @@ __device__ __forceinline__ bool attend(const AttnArgs& p, int b, int h, int qt) 
 #pragma unroll
     for (int qb = 0; qb < kQB; ++qb)
 #pragma unroll
-      for (int j = 0; j < 2; ++j) {
+      for (int j = 0; j < kJ; ++j) {
         w.mref[qb][j] = 0.f;
         init_extras(qb, j, 0.f);
       }
@@ -812,18 +830,18 @@ __device__ __forceinline__ bool attend(const AttnArgs& p, int b, int h, int qt) 
     const int valid0 = ntiles == 1 ? last_valid : kTileRows;
 #pragma unroll
     for (int qb = 0; qb < kQB; ++qb) {
-      w.mref[qb][0] = 0.f;
-      w.mref[qb][1] = 0.f;
-      f32x4 s[4];
-      score_unit<kGen>(w, qb, s);
-      if (valid0 < 32) mask_unit(s, 0, valid0, G);
 #pragma unroll
-      for (int j = 0; j < 2; ++j) {
+      for (int j = 0; j < kJ; ++j) w.mref[qb][j] = 0.f;
+      f32x4 s[2 * kJ];
+      score_unit<kGen, kQB, kJ>(w, qb, s);
+      if (valid0 < 32) mask_unit<kJ>(s, 0, valid0, G);
+#pragma unroll
+      for (int j = 0; j < kJ; ++j) {
         float mx = s[j][0];
 #pragma unroll
         for (int kt = 0; kt < 2; ++kt)
 #pragma unroll
-          for (int r = 0; r < 4; ++r) mx = fmaxf(mx, s[2 * kt + j][r]);
+          for (int r = 0; r < 4; ++r) mx = fmaxf(mx, s[kJ * kt + j][r]);
         mx = quad_max(mx);
         mx = fmaxf(mx, fmaxf(l_self[qb][j], l_mean[qb][j]));
         // a NaN or infinite score cannot serve as reference; the row's result is NaN anyway
@@ -834,14 +852,14 @@ __device__ __forceinline__ bool attend(const AttnArgs& p, int b, int h, int qt) 
     }
   };
 
-  const bool done = key_loop<kSrc, kGen>(w, lds, src, ntiles, last_valid, tid, wave, fa, G,
-                                         first_tile);
-  float l_fin[kQB][2];
+  const bool done = key_loop<kSrc, kGen, kQB, kJ>(w, lds, src, ntiles, last_valid, tid, wave, fa, G,
+                                                  first_tile);
+  float l_fin[kQB][kJ];
   bool unsafe = false;
 #pragma unroll
   for (int qb = 0; qb < kQB; ++qb)
 #pragma unroll
-    for (int j = 0; j < 2; ++j) {
+    for (int j = 0; j < kJ; ++j) {
       l_fin[qb][j] = kGen ? quad_sum(w.la[qb][j]) : w.L[qb][j][0];
       // a sum outside [2^-90, 2^90] (or NaN): the unreferenced exponentials were not safe
       unsafe = unsafe || !(l_fin[qb][j] < kSumHi) || !(l_fin[qb][j] > kSumLo);
@@ -854,15 +872,15 @@ __device__ __forceinline__ bool attend(const AttnArgs& p, int b, int h, int qt) 
   // ---- normalise and store ----
   // A lane holds four consecutive channels of one query per accumulator tile: stored from there,
   // every instruction would scatter 8-byte pieces over 16 rows that lie 2*H*64 bytes apart.
-  // Each wavefront instead turns its tile, 32 queries at a time, through a private part of the
+  // Each wavefront instead turns its tile, a query block at a time, through a private part of the
   // (now idle) K/V LDS and writes whole 128-byte (query, head) rows, eight per instruction.
   __syncthreads();  // every wavefront is done with the K/V tiles
-  uint16_t* epi = smem + wave * (32 * kEpiStride);
+  uint16_t* epi = smem + wave * (16 * kJ * kEpiStride);
 #pragma unroll
   for (int qb = 0; qb < kQB; ++qb) {
-    const int64_t q0 = q_wave + qb * 32;
+    const int64_t q0 = q_wave + qb * kJ * 16;
 #pragma unroll
-    for (int j = 0; j < 2; ++j) {
+    for (int j = 0; j < kJ; ++j) {
       const float l = l_fin[qb][j];
       const float inv = 1.0f / l;
 #pragma unroll
@@ -873,7 +891,7 @@ __device__ __forceinline__ bool attend(const AttnArgs& p, int b, int h, int qt) 
         o2[1] = pack_bf16(w.O[qb][j][dt][2] * inv, w.O[qb][j][dt][3] * inv);
         *reinterpret_cast<u32x2*>(epi + (16 * j + c) * kEpiStride + d0) = o2;
       }
-      if (p.lse && G == 0 && q0 + 16 * j + c < g.NQ)
+      if (p.lse && G == 0 && q0 + 16 * j + c < q_end)
         p.lse[((int64_t)b * g.H + h) * g.NQ + q0 + 16 * j + c] =
             ((kGen ? w.mref[qb][j] : 0.f) + log2f(l)) * kLn2;
     }
@@ -882,11 +900,11 @@ __device__ __forceinline__ bool attend(const AttnArgs& p, int b, int h, int qt) 
     __builtin_amdgcn_wave_barrier();
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront", "local");
 #pragma unroll
-    for (int i = 0; i < 4; ++i) {
+    for (int i = 0; i < 2 * kJ; ++i) {
       const int row = i * 8 + (lane >> 3);
       const int64_t q = q0 + row;
       const u32x4 o4 = *reinterpret_cast<const u32x4*>(epi + row * kEpiStride + (lane & 7) * 8);
-      if (q < g.NQ)
+      if (q < q_end)
         *reinterpret_cast<u32x4*>(p.O + (((int64_t)b * g.NQ + q) * g.H + h) * kHeadDim +
                                   (lane & 7) * 8) = o4;
     }
@@ -897,69 +915,191 @@ __device__ __forceinline__ bool attend(const AttnArgs& p, int b, int h, int qt) 
   return true;
 }
 
+// position in a launch list of n tiles per pair -> (pair, tile of the pair).  Consecutive ids go
+// to consecutive XCDs.  Whole pairs are dealt out one per XCD, so that an XCD streams one
+// key/value set at a time through its own L2; the npairs % 8 pairs that are left share the XCDs
+// between them, each XCD taking an equal, contiguous run of their tiles.  (Dealing those out whole
+// as well left XCDs idle: ordinary attention over 24 frames of 28x37 patches with 12 heads took
+// 2.12 ms, with the shared run 1.52.)
+struct TileList {
+  int n;         // tiles per pair
+  int whole;     // tiles of an XCD's whole pairs
+  int rest;      // tiles of an XCD's run over the remaining pairs
+  int groups;    // workgroups of the list
+};
+__host__ __device__ inline TileList tile_list(int npairs, int n) {
+  TileList l;
+  l.n = n;
+  l.whole = npairs / kXcds * n;
+  l.rest = (npairs % kXcds * n + kXcds - 1) / kXcds;
+  l.groups = kXcds * (l.whole + l.rest);
+  return l;
+}
+__device__ __forceinline__ bool list_tile(const TileList& l, int npairs, int bid, int& pair, int& i) {
+  const int xcd = bid % kXcds;
+  const int seq = bid / kXcds;
+  if (seq < l.whole) {
+    pair = (seq / l.n) * kXcds + xcd;
+    i = seq % l.n;
+  } else {
+    const int u = seq - l.whole + xcd * l.rest;
+    if (u >= npairs % kXcds * l.n) return false;  // uniform for the whole workgroup
+    pair = npairs / kXcds * kXcds + u / l.n;
+    i = u % l.n;
+  }
+  return true;
+}
+__host__ __device__ inline TileList first_list(const TilePlan& t, int npairs) {
+  return tile_list(npairs, t.n_full + (t.tails_last ? 0 : t.n_tail));
+}
+__host__ __device__ inline TileList second_list(const TilePlan& t, int npairs) {
+  return tile_list(npairs, t.tails_last ? t.n_tail : 0);
+}
+
+// What a workgroup does: queries q_begin .. q_end - 1 of batch element b, head h.
+struct Work {
+  int b, h;
+  int64_t q_begin, q_end;
+  bool tail;
+};
+__device__ __forceinline__ bool workgroup_work(const AttnArgs& p, Work& w) {
+  const TilePlan& t = p.plan;
+  const TileList first = first_list(t, p.npairs);
+  int pair, i;
+  if ((int)blockIdx.x < first.groups) {
+    if (!list_tile(first, p.npairs, blockIdx.x, pair, i)) return false;
+  } else {
+    if (!list_tile(second_list(t, p.npairs), p.npairs, blockIdx.x - first.groups, pair, i)) return false;
+    i += t.n_full;
+  }
+  w.b = pair / p.g.H;
+  w.h = pair % p.g.H;
+  w.tail = i >= t.n_full;
+  w.q_begin = w.tail ? (int64_t)t.n_full * kQTile + (int64_t)(i - t.n_full) * t.tail_q
+                     : (int64_t)i * kQTile;
+  w.q_end = min(p.g.NQ, w.q_begin + (w.tail ? t.tail_q : kQTile));
+  return true;
+}
+
 // A workgroup whose fast pass failed leaves this pattern (four bf16 NaNs with distinct payloads)
 // in the first four channels of its first output row and stores nothing else; the second kernel
 // redoes exactly the workgroups that carry it.  Should a correct result ever equal the pattern,
 // the second kernel recomputes that workgroup, which is harmless.
 constexpr uint64_t kRedoMark = 0x7F997FC37FA57FC1ull;
 
-__device__ __forceinline__ uint64_t* redo_slot(const AttnArgs& p, int b, int h, int qt) {
-  return reinterpret_cast<uint64_t*>(p.O + (((int64_t)b * p.g.NQ + (int64_t)qt * kQTile) * p.g.H + h) *
-                                               kHeadDim);
+__device__ __forceinline__ uint64_t* redo_slot(const AttnArgs& p, const Work& w) {
+  return reinterpret_cast<uint64_t*>(p.O + (((int64_t)w.b * p.g.NQ + w.q_begin) * p.g.H + w.h) * kHeadDim);
 }
 
-// workgroup -> ((batch, head) pair, query tile).  Consecutive ids go to consecutive XCDs.  Whole
-// pairs are dealt out one per XCD, so that an XCD streams one key/value set at a time through its
-// own L2; the npairs % 8 pairs that are left share the XCDs between them, each XCD taking an equal,
-// contiguous run of their tiles.  (Dealing those out whole as well left XCDs idle: ordinary
-// attention over 24 frames of 28x37 patches with 12 heads took 2.12 ms, with the shared run 1.52.)
-struct TileMap {
-  int per_xcd_whole;  // tiles of an XCD's whole pairs
-  int per_xcd_rest;   // tiles of an XCD's run over the remaining pairs
-};
-__host__ __device__ inline TileMap tile_map(int npairs, int nqt) {
-  TileMap m;
-  m.per_xcd_whole = npairs / kXcds * nqt;
-  m.per_xcd_rest = (npairs % kXcds * nqt + kXcds - 1) / kXcds;
-  return m;
-}
-__device__ __forceinline__ bool workgroup_tile(const AttnArgs& p, int& b, int& h, int& qt) {
-  const int bid = blockIdx.x;
-  const int xcd = bid % kXcds;
-  const int seq = bid / kXcds;
-  const TileMap m = tile_map(p.npairs, p.nqt);
-  int pair;
-  if (seq < m.per_xcd_whole) {
-    pair = (seq / p.nqt) * kXcds + xcd;
-    qt = seq % p.nqt;
-  } else {
-    const int u = seq - m.per_xcd_whole + xcd * m.per_xcd_rest;
-    if (u >= p.npairs % kXcds * p.nqt) return false;  // uniform for the whole workgroup
-    pair = p.npairs / kXcds * kXcds + u / p.nqt;
-    qt = u % p.nqt;
-  }
-  b = pair / p.g.H;
-  h = pair % p.g.H;
-  return true;
-}
-
-template <int kSrc>
+// kTailQ: queries of the launch's narrow workgroups (0: it has none).
+template <int kSrc, int kTailQ>
 __global__ __launch_bounds__(kAttnThreads, kBlocksPerCu) void sga_attn_kernel(AttnArgs p) {
-  int b, h, qt;
-  if (!workgroup_tile(p, b, h, qt)) return;
-  if (!attend<kSrc, false>(p, b, h, qt) && threadIdx.x == 0) *redo_slot(p, b, h, qt) = kRedoMark;
+  Work w;
+  if (!workgroup_work(p, w)) return;
+  bool done;
+  if (kTailQ != 0 && w.tail) {
+    constexpr int kTailQB = kTailQ == 192 ? 3 : 2;  // blocks of one 16-query tile
+    done = attend<kSrc, false, kTailQB, 1>(p, w.b, w.h, w.q_begin, w.q_end);
+  } else {
+    done = attend<kSrc, false, 2, 2>(p, w.b, w.h, w.q_begin, w.q_end);
+  }
+  if (!done && threadIdx.x == 0) *redo_slot(p, w) = kRedoMark;
 }
 
 // The general path is a kernel of its own, launched behind the first on the same stream: it is
 // rarely needed, starts over from the workgroup's inputs, and this way does not weigh on the
-// register allocation of the fast path.  Workgroups without the mark leave at once.
+// register allocation of the fast path.  Workgroups without the mark leave at once; narrow ones
+// are redone at full width with the queries beyond their own left out.
 template <int kSrc>
 __global__ __launch_bounds__(kAttnThreads, kBlocksPerCu) void sga_attn_general_kernel(AttnArgs p) {
-  int b, h, qt;
-  if (!workgroup_tile(p, b, h, qt)) return;
-  if (*redo_slot(p, b, h, qt) != kRedoMark) return;  // same value in every lane
+  Work w;
+  if (!workgroup_work(p, w)) return;
+  if (*redo_slot(p, w) != kRedoMark) return;  // same value in every lane
   __syncthreads();  // every wavefront has read the mark before any of them overwrites it
-  attend<kSrc, true>(p, b, h, qt);
+  attend<kSrc, true, 2, 2>(p, w.b, w.h, w.q_begin, w.q_end);
+}
+
+// Launch plan: which workgroups a pair's queries are cut into.
+//
+// A workgroup's whole key loop is one piece of work, so a launch of a few rounds loses up to a
+// round to its last, partly filled one, and a short sequence pays for up to 255 queries that do
+// not exist.  Narrow workgroups (192 or 128 queries) lose less there; they are not free, because
+// every K/V fragment then feeds fewer products.  Measured over 121 key tiles with 16 pairs, in
+// units of what two full-width workgroups on one CU take (201 us): a pair of 192 0.79, of 128 0.56;
+// one alone on its CU 0.53 (256 queries), 0.45 (192), 0.36 (128).  The plan takes the narrow
+// tail that the cost model below puts at least 1.5 % ahead of full-width workgroups alone.
+// Measured with it: 10 frames of 37x37 patches, 16 heads, 367 us instead of 401 (attention
+// alone); two frames of 16x16 patches 27.6 instead of 33.3 (the whole layer).
+struct TileCost {
+  int queries;
+  double paired, alone;  // on a CU that holds two workgroups / this one only
+};
+static const TileCost kFullCost = {kQTile, 1.0, 0.535};
+static const TileCost kTailCosts[] = {{192, 0.79, 0.45}, {128, 0.565, 0.355}};
+
+// Time of a CU that runs `full` full-width and then `tail` narrow workgroups, two at a time.
+static double cu_time(int64_t full, int64_t tail, const TileCost& c) {
+  double t = 0.5 * (full * kFullCost.paired + tail * c.paired);
+  if ((full + tail) & 1) t += tail ? c.alone - 0.5 * c.paired : kFullCost.alone - 0.5 * kFullCost.paired;
+  return t;
+}
+// Time of a launch: the full-width workgroups are dealt out evenly, each narrow one goes to the
+// CU that is free first.
+static double launch_time(int64_t full, int64_t tail, const TileCost& c) {
+  const int64_t extra = full % kCus;
+  const int64_t cus[2] = {kCus - extra, extra};
+  const int64_t f[2] = {full / kCus, full / kCus + 1};
+  int64_t t[2] = {0, 0};
+  double end = cu_time(f[extra ? 1 : 0], 0, c);
+  while (tail > 0) {
+    const int k = (cus[1] > 0 && cu_time(f[1], t[1], c) < cu_time(f[0], t[0], c)) ? 1 : 0;
+    ++t[k];
+    tail -= cus[k];
+    const double now = cu_time(f[k], t[k], c);
+    end = now > end ? now : end;
+  }
+  return end;
+}
+
+static TilePlan plan_tiles(int64_t NQ, int npairs, int64_t key_tiles) {
+  const int64_t most = NQ / kQTile;
+  TilePlan best = {(int)((NQ + kQTile - 1) / kQTile), 0, 0, 0};
+  if (npairs * NQ > INT32_MAX) return best;  // far past the sizes at which a tail matters
+  // With at least a pair per CU the rounds are many, and what is left to gain are the queries
+  // that do not exist; the tails then follow their pair's other tiles, whose keys they share.
+  // Per-frame attention, 90 frames of 37x37 patches: 710 us instead of 728.  Under eight key tiles
+  // the second code path costs more than the idle queries: 50 frames of 16x16, 51.0 against 50.2.
+  const bool by_pair = npairs >= kCus;
+  if (by_pair && key_tiles < 8) return best;
+  double least = by_pair ? (double)best.n_full : launch_time(npairs * (int64_t)best.n_full, 0, kFullCost);
+  least *= 0.985;
+  // full-width workgroups per pair: all that fit, one fewer, and what fills whole rounds
+  const int64_t round = 2 * kCus, rounds = npairs * most / round;
+  const int64_t tries[] = {most, most - 1, rounds * round / npairs, (rounds - 1) * round / npairs};
+  for (int i = 0; i < (by_pair ? 2 : 4); ++i) {
+    const int64_t n = tries[i], left = NQ - n * kQTile;
+    if (n < 0 || left == 0) continue;
+    for (const TileCost& c : kTailCosts) {
+      const int64_t m = (left + c.queries - 1) / c.queries;
+      const double t = by_pair ? n + m * c.paired : launch_time(npairs * n, npairs * m, c);
+      if (t < least) {
+        least = t;
+        best = {(int)n, (int)m, c.queries, by_pair ? 0 : 1};
+      }
+    }
+  }
+  return best;
+}
+
+template <int kSrc>
+static void launch_source(const AttnArgs& p, hipStream_t st) {
+  const dim3 grid((unsigned)(first_list(p.plan, p.npairs).groups + second_list(p.plan, p.npairs).groups));
+  const dim3 block(kAttnThreads);
+  const int tail_q = p.plan.n_tail ? p.plan.tail_q : 0;
+  if (tail_q == 0) hipLaunchKernelGGL((sga_attn_kernel<kSrc, 0>), grid, block, 0, st, p);
+  else if (tail_q == 192) hipLaunchKernelGGL((sga_attn_kernel<kSrc, 192>), grid, block, 0, st, p);
+  else hipLaunchKernelGGL((sga_attn_kernel<kSrc, 128>), grid, block, 0, st, p);
+  hipLaunchKernelGGL(sga_attn_general_kernel<kSrc>, grid, block, 0, st, p);
 }
 
 hipError_t launch_attn(const Geom& g, uint32_t flags, float scale, float mean_bias, const void* Q,
@@ -967,13 +1107,10 @@ hipError_t launch_attn(const Geom& g, uint32_t flags, float scale, float mean_bi
                        const float* kmean, const float* vmean, void* O, float* lse, hipStream_t st,
                        const uint32_t* kept_bits, const int32_t* nd_dev, int src_mode,
                        const int32_t* list, int64_t list_stride) {
-  const int nqt = (int)((g.NQ + kQTile - 1) / kQTile);
   const int npairs = g.B * g.H;
-  // (the bound is checked with whole pairs per XCD throughout, which is at least the grid)
-  if ((int64_t)((npairs + kXcds - 1) / kXcds) * kXcds * nqt > 0x7FFFFFFF)
+  // the bound on the grid, with whole pairs per XCD throughout (narrow workgroups: plan_tiles)
+  if ((int64_t)((npairs + kXcds - 1) / kXcds) * kXcds * ((g.NQ + kQTile - 1) / kQTile) > 0x7FFFFFFF)
     return hipErrorInvalidConfiguration;
-  const TileMap map = tile_map(npairs, nqt);
-  const int64_t groups = (int64_t)kXcds * (map.per_xcd_whole + map.per_xcd_rest);
   // indexed rows are addressed with 32-bit byte offsets from the (batch, head) base, formed by
   // a 24-bit multiplication of token id and row length
   if (src_mode == kSrcIndexed && ((uint64_t)g.NQ * g.H * (kHeadDim * 2) > 0xFFFFFFFFull ||
@@ -994,23 +1131,15 @@ hipError_t launch_attn(const Geom& g, uint32_t flags, float scale, float mean_bi
   p.vmean = vmean;
   p.O = (uint16_t*)O;
   p.lse = lse;
-  p.nqt = nqt;
   p.npairs = npairs;
+  p.plan = plan_tiles(g.NQ, npairs, g.M_pad / kTileRows);
   p.kept_bits = kept_bits;
   p.nd_dev = nd_dev;
   p.list = list;
   p.list_stride = list_stride;
-  const dim3 grid((unsigned)groups), block(kAttnThreads);
-  if (src_mode == kSrcCompact) {
-    hipLaunchKernelGGL(sga_attn_kernel<kSrcCompact>, grid, block, 0, st, p);
-    hipLaunchKernelGGL(sga_attn_general_kernel<kSrcCompact>, grid, block, 0, st, p);
-  } else if (src_mode == kSrcRows) {
-    hipLaunchKernelGGL(sga_attn_kernel<kSrcRows>, grid, block, 0, st, p);
-    hipLaunchKernelGGL(sga_attn_general_kernel<kSrcRows>, grid, block, 0, st, p);
-  } else {
-    hipLaunchKernelGGL(sga_attn_kernel<kSrcIndexed>, grid, block, 0, st, p);
-    hipLaunchKernelGGL(sga_attn_general_kernel<kSrcIndexed>, grid, block, 0, st, p);
-  }
+  if (src_mode == kSrcCompact) launch_source<kSrcCompact>(p, st);
+  else if (src_mode == kSrcRows) launch_source<kSrcRows>(p, st);
+  else launch_source<kSrcIndexed>(p, st);
   return hipGetLastError();
 }
 

@@ -4,9 +4,10 @@ import numpy as np
 import pytest
 import torch
 
+from oracle import sga_oracle as orc
 from paper_2512_02541_amd import binding as agg
 from paper_2512_02541_amd import harness, inputs
-from test_gpu_parity import _idx_case, run_case
+from test_gpu_parity import _idx_case, check_output, oshape, run_case
 
 pytestmark = pytest.mark.gpu
 
@@ -21,3 +22,47 @@ def test_pairs_around_the_xcd_count(B, H, nq):
     q, k, v = inputs.iid_qkv(B, nq, H, 64, seed=5000 + 100 * B + H, device="cuda")
     run_case(shape, q, k, v, what="pairs %d" % (B * H))
     _idx_case(shape, q, k, v, "pairs %d" % (B * H))
+
+
+# (B, queries, H, column stride): the strides leave 70 to 150 keys, so that every row can be checked
+TAILS = [
+    (1, 1000, 16, 9),      # narrow workgroups only (128 queries)
+    (1, 9192, 16, 97),     # whole rounds of full-width workgroups, then 128-query ones
+    (1, 13740, 16, 97),    # ... then 192-query ones
+    (1, 24984, 12, 301),   # ... over pairs that share the XCDs
+    (1, 8193, 16, 97),     # one query beyond whole rounds
+    (2, 2049, 8, 31),      # two batch elements
+]
+
+
+@pytest.mark.parametrize("extreme", [False, True])
+@pytest.mark.parametrize("case", TAILS)
+def test_narrow_tail_workgroups(case, extreme):
+    """Launches that end in narrow workgroups, compacted and index-driven.  `extreme`: one query in
+    211 leaves the fast path's range, so that full-width and narrow workgroups alike are redone.
+    Those queries are 32 times their own key: their own logit is 32 |k|^2 / 8, about 256 and above
+    128, every other one at most 32 |k| |k'| cos / 8, a normal of deviation 32.  A rounding of the
+    query operand moves a logit by 2^-9 of that, at most 1, so their own column keeps all the
+    weight (an arbitrary query scaled up would not: it ties two columns up to that error)."""
+    B, nq, H, s_w = case
+    shape = agg.make_shape(B, 1, 1, nq, 0, H, 64, 1, s_w, 0)
+    q, k, v = inputs.iid_qkv(B, nq, H, 64, seed=6100 + nq, device="cuda")
+    if extreme:
+        q[:, ::211] = 32 * k[:, ::211]
+    run_case(shape, q, k, v, what="tail %s" % (case,))
+    _idx_case(shape, q, k, v, "tail %s" % (case,))
+
+
+@pytest.mark.parametrize("L", [449, 600, 700, 769])
+def test_narrow_tail_per_frame(L):
+    """A pair per CU and more: each pair's narrow workgroup (128 queries at 449, 600 and 769, 192 at
+    700) follows its full-width ones.  449 keys are the fewest that take this order."""
+    shape = agg.make_shape(1, 16, 1, L, 0, 16, 64, 1, 1, 0, flags=0)
+    q, k, v = inputs.iid_qkv(1, shape.NQ, 16, 64, seed=6600 + L, device="cuda")
+    O, lse = harness.frame_forward(shape, q, k, v)
+    torch.cuda.synchronize()
+    rows = np.concatenate([f * L + np.arange(256 * (L // 256) - 40, L) for f in (0, 7, 15)])
+    qb, kb, vb = (inputs.bf16_bits(t) for t in (q, k, v))
+    want_o, want_lse = orc.frame_rows(oshape(shape), qb, kb, vb, rows)
+    got_lse = lse.permute(1, 0, 2).reshape(1, 16, shape.NQ)
+    check_output(O, got_lse, want_o, want_lse, rows, "frame tail %d" % L, q, k, shape.scale)
