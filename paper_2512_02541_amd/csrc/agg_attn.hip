@@ -60,6 +60,7 @@
 //     (batch, head): all workgroups resident on one XCD read the same K/V
 //     stream and share it through that XCD's L2.
 #include "agg_internal.h"
+#include "agg_lds_copy.h"
 
 namespace agg {
 
@@ -118,35 +119,6 @@ __device__ __forceinline__ float pair_sum(float x) {
   const auto r = __builtin_amdgcn_permlane32_swap(b, b, false, false);
   return __uint_as_float(r[0]) + __uint_as_float(r[1]);
 }
-
-// Workgroup barrier that orders LDS traffic only: global loads issued for a later tile
-// stay in flight across it.
-__device__ __forceinline__ void lds_barrier() {
-  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
-  __builtin_amdgcn_s_barrier();
-  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
-}
-
-// Asynchronous copy global -> LDS without passing through registers: lane i of the wavefront
-// lands the 16 bytes at `base + voff(i)` at LDS address m0 + 16 i.  Written as assembly so that
-// the compiler's wait-count pass does not serialise later LDS reads of OTHER buffers behind this
-// copy; the loop waits for it explicitly before the barrier.  M0 is a register the compiler
-// reserves and sets right before each of its own uses; this kernel has none (a build test checks
-// that no compiler-emitted instruction of it reads M0).
-__device__ __forceinline__ void dma16(const void* base, uint32_t voff, uint32_t m0) {
-  asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, %1"
-               :
-               : "v"(voff), "s"(base), "s"(m0)
-               : "memory");
-}
-// a pointer every lane agrees on, as two scalar registers (what the copy's base operand needs)
-__device__ __forceinline__ const uint16_t* uniform_ptr(const uint16_t* q) {
-  const uint64_t v = (uint64_t)(uintptr_t)q;
-  const uint32_t lo = __builtin_amdgcn_readfirstlane((uint32_t)v);
-  const uint32_t hi = __builtin_amdgcn_readfirstlane((uint32_t)(v >> 32));
-  return (const uint16_t*)(uintptr_t)(((uint64_t)hi << 32) | lo);
-}
-__device__ __forceinline__ void wait_vm0() { __builtin_amdgcn_s_waitcnt(0x0F70); }  // vmcnt(0) only
 
 #define AGG_MFMA16(a, b, c) __builtin_amdgcn_mfma_f32_16x16x32_bf16((a).h, (b).h, (c), 0, 0, 0)
 
@@ -252,7 +224,6 @@ __device__ __forceinline__ void exp_unit_sum(const f32x4 (&S)[2 * kJ], Frag (&P)
 enum { kSrcCompact = 0, kSrcRows = 1, kSrcIndexed = 2 };
 
 typedef short s16x4 __attribute__((ext_vector_type(4)));
-typedef __attribute__((address_space(3))) char lds_char;
 
 // chunk swizzle of a K row in the row modes: the 16 rows a lane group reads (i, i + 16 for eight
 // consecutive i) must fall on 16 different 16-byte slots of the 256-byte bank period

@@ -4,12 +4,12 @@
 // They are a few percent of a block's time next to attention over 10^5..10^6 tokens and
 // follow the MFMA conventions of the attention kernel.
 #include "agg_internal.h"
+#include "agg_lds_copy.h"
 
 namespace agg {
 
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
-typedef float f32x16 __attribute__((ext_vector_type(16)));
 typedef float f32x2 __attribute__((ext_vector_type(2)));
 typedef float f32x4 __attribute__((ext_vector_type(4)));
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
@@ -103,184 +103,270 @@ __global__ __launch_bounds__(kLnThreads) void layernorm_kernel(const uint16_t* _
 
 // ---------------------------------------------------------------------------
 // Linear layer  Y[m, n] = sum_k A[m, k] W[n, k] + bias[n] (+ R[m, n]),  bf16 in/out,
-// fp32 accumulation on v_mfma_f32_32x32x16_bf16.  A: [rows, K] row-major; W: [N, K]
+// fp32 accumulation on v_mfma_f32_16x16x32_bf16.  A: [rows, K] row-major; W: [N, K]
 // row-major (one row per output channel), so both operands are contiguous along k.
-// One workgroup (8 wavefronts) computes a 256 x 256 tile with 64-wide k steps,
-// double-buffered in LDS (128 KiB) through registers; each wavefront owns 64 tokens x 128
-// channels: six fragment reads feed eight MFMAs, and a tile's operands are fetched from L2
-// half as often as with 128 x 128 tiles.  LDS rows are 128
-// bytes with the 16-byte chunk index XOR-ed by the row pair's number so that both the
-// row-wise fills and the fragment reads spread over all banks.  The product is formed
-// transposed (W rows as the MFMA A operand): a lane ends up with four consecutive output
-// channels of one token, and the epilogue turns the tile through LDS so that rows leave in
-// 128-byte runs.
-// Requires K % 64 == 0 and N % 8 == 0.
+// Requires K % 64 == 0 and N % 64 == 0.
+//
+// One workgroup (8 wavefronts) walks a list of 256 x 256 tiles, alone on its CU, or of 128 x 128
+// tiles, two to a CU (launch_linear chooses); in a large tile a wavefront owns 64 tokens x 128
+// channels, so that twelve fragment reads feed 32 MFMAs.
+// k advances 64 at a time: whole 128-byte lines are fetched (with 32 the copies took twice the
+// requests and bounded the kernel: 970 us without a single LDS read).  The operands go global ->
+// LDS without passing through registers, into five slots used in turn by A(0) W(0) A(1) W(1) ...:
+// a step works on two of them while the next W and the next two A are on their way, which is as
+// deep as 160 KiB allows; the tokens, which come from HBM, get the longer lead.  The list goes on over tile
+// borders: the next tile's operands are under way during a tile's last steps, and its stores drain
+// under the next tile's first.
+// LDS rows are 128 bytes with the 16-byte chunk number XOR-ed by bits 1..3 of the row, which
+// spreads the 16 rows of a fragment read over all 64 banks.
+// W's rows are copied into LDS in an order that leaves a lane with eight consecutive channels of
+// a token: bias and residual are added in float before the one rounding, and a store instruction
+// writes four 256-byte runs.
 //
 // One launch serves up to three weight matrices applied to the same input (the Q, K and V
-// projections): their output tiles of one token tile are neighbours in the launch order and
-// run on the same XCD, so a token tile is fetched from HBM once and then served by that
-// XCD's L2 to all of them.
+// projections): their output tiles of one token tile are neighbours in an XCD's list, so that a
+// token tile is fetched from HBM once and then served by that XCD's L2 to all of them.
+//
+// Measured at 137 400 rows, C = 1024 (us for Q/K/V and for the output projection): 1060 + 420
+// before (256 x 256 tiles through registers, one workgroup per tile); 1040 + 400 with 256 x 128
+// tiles, two to a CU, 32-wide k; 855 + 360 persistent with two 64 KiB stages; 817 + 325 as it is
+// (1.06 PFLOP/s).  Without its copies it takes 610, without copies and stores 552, the products
+// alone 480; spreading a step's copies over its products, grouping token tiles, touching lines
+// ahead of the copies and streaming stores made it no faster or slower.
 // ---------------------------------------------------------------------------
 constexpr int kGemmThreads = 512;
-constexpr int kTM = 256, kTN = 256, kTK = 64;
+constexpr int kTK = 64;
 constexpr int kGemmXcds = 8;
-constexpr int kEpiStride = 64 + 4;  // floats per token row of the epilogue's LDS tile (padded)
-constexpr int kStage = (kTM * 8) / kGemmThreads;  // 16-byte chunks per thread and operand (4)
+constexpr int kGemmCus = 256;
+constexpr int kSlots = 5;
 
-// LDS has 64 banks of 4 bytes: a 16-byte access per lane is served 16 lanes at a time, which
-// must then fall on 16 different 16-byte slots of the 256-byte bank period.  Two 128-byte rows
-// share a period; XOR-ing the chunk with the row PAIR's number spreads 16 consecutive rows of
-// one chunk column (a fragment read) as well as the 16 chunks of a row pair (a fill).
-__device__ inline int swz(int row, int chunk) {
-  return (row >> 1) * 16 + ((((row & 1) << 3) | chunk) ^ ((row >> 1) & 7));
-}
-
-template <bool kResidual>
-__global__ __launch_bounds__(kGemmThreads, 1) void linear_kernel(
+// kEdge: 256 or 128, the tile's tokens and channels
+template <int kEdge, bool kResidual>
+__global__ __launch_bounds__(kGemmThreads, kEdge == 256 ? 2 : 4) void linear_kernel(
     const uint16_t* __restrict__ A, LinearOuts outs, const uint16_t* __restrict__ R, int64_t rows,
     int N, int K, int gm, int gn) {
-  __shared__ __align__(16) u32x4 sA[2][kTM * 8];
-  __shared__ __align__(16) u32x4 sW[2][kTN * 8];
-  // workgroup id -> (token tile, output tile): consecutive ids go to consecutive XCDs; an XCD
-  // walks all output tiles of one token tile before it moves to its next token tile
+  constexpr int kMT = kEdge / 64;              // 16-token tiles of a wavefront; also copies per slot of A
+  constexpr int kNT = kEdge / 32;              // its 16-channel tiles
+  constexpr int kSlotBytes = kEdge * kTK * 2;  // one step's rows of A or of W
+  constexpr int kCopies = kEdge / 64;          // copies of a wavefront per slot
+  constexpr int kRows = kEdge / 8;             // LDS rows of a slot that a wavefront copies
+  constexpr int kTileStores = 4 * kMT;         // store instructions of a wavefront per tile
+  __shared__ __align__(16) char sm[kSlots * kSlotBytes];
   const int xcd = blockIdx.x % kGemmXcds;
-  const int seq = blockIdx.x / kGemmXcds;
   const int per_m = gn * outs.count;
-  const int mt = (seq / per_m) * kGemmXcds + xcd;
-  if (mt >= gm) return;  // uniform for the workgroup, before any barrier
-  const int nt_all = seq % per_m;
-  const int which = nt_all / gn;
-  const uint16_t* __restrict__ W = outs.W[which];
-  const float* __restrict__ bias = outs.bias[which];
-  uint16_t* __restrict__ Y = outs.Y[which];
   const int tid = threadIdx.x;
   const int lane = tid & 63;
-  const int wave = tid >> 6;
-  const int l32 = lane & 31;
-  const int g2 = lane >> 5;
-  const int wm = (wave & 3) * 64;    // this wavefront's 64 token rows inside the tile
-  const int wn = (wave >> 2) * 128;  // and its 128 output channels
-  const int64_t m0 = (int64_t)mt * kTM;
-  const int n0 = (nt_all % gn) * kTN;
-
-  // staging: 256 rows x 8 chunks per operand = 2048 chunks, 4 per thread
-  u32x4 ra[kStage], rw[kStage];
-  auto gload = [&](int k0) {
-#pragma unroll
-    for (int i = 0; i < kStage; ++i) {
-      const int c = tid + i * kGemmThreads;
-      const int r = c >> 3, j = c & 7;
-      int64_t am = m0 + r;
-      if (am >= rows) am = rows - 1;  // tail rows repeat the last row, never stored
-      int wn_ = n0 + r;
-      if (wn_ >= N) wn_ = N - 1;
-      ra[i] = *reinterpret_cast<const u32x4*>(A + am * K + k0 + j * 8);
-      rw[i] = *reinterpret_cast<const u32x4*>(W + (int64_t)wn_ * K + k0 + j * 8);
-    }
-  };
-  auto lstore = [&](int buf) {
-#pragma unroll
-    for (int i = 0; i < kStage; ++i) {
-      const int c = tid + i * kGemmThreads;
-      const int r = c >> 3, j = c & 7;
-      sA[buf][swz(r, j)] = ra[i];
-      sW[buf][swz(r, j)] = rw[i];
-    }
-  };
-
-  f32x16 acc[4][2];  // [channel block][token block]
-#pragma unroll
-  for (int a = 0; a < 4; ++a)
-#pragma unroll
-    for (int b = 0; b < 2; ++b)
-#pragma unroll
-      for (int r = 0; r < 16; ++r) acc[a][b][r] = 0.f;
-
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int c = lane & 15;
+  const int G = lane >> 4;
+  const int wm = (wave & 3) * (16 * kMT);  // this wavefront's tokens inside the tile
+  const int wn = (wave >> 2) * (16 * kNT); // and its output channels
   const int nk = K / kTK;
-  gload(0);
-  lstore(0);
-  __syncthreads();
-  for (int kt = 0; kt < nk; ++kt) {
-    const int buf = kt & 1;
-    if (kt + 1 < nk) gload((kt + 1) * kTK);
-    // fragments of sub-step ks+1 are requested before the MFMAs of sub-step ks are issued, and
-    // the scheduler is kept from sinking those reads back down next to their use
-    Frag fw[2][4], fa[2][2];
-    auto load_frags = [&](int ks, int set) {
-#pragma unroll
-      for (int a = 0; a < 4; ++a) fw[set][a].u = sW[buf][swz(wn + a * 32 + l32, ks * 2 + g2)];
-#pragma unroll
-      for (int b = 0; b < 2; ++b) fa[set][b].u = sA[buf][swz(wm + b * 32 + l32, ks * 2 + g2)];
-    };
-    load_frags(0, 0);
-#pragma unroll
-    for (int ks = 0; ks < 4; ++ks) {
-      if (ks < 3) load_frags(ks + 1, (ks + 1) & 1);
-      __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-      for (int a = 0; a < 4; ++a)
-#pragma unroll
-        for (int b = 0; b < 2; ++b)
-          acc[a][b] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fw[ks & 1][a].h, fa[ks & 1][b].h,
-                                                              acc[a][b], 0, 0, 0);
-      __builtin_amdgcn_sched_barrier(0);
-    }
-    if (kt + 1 < nk) lstore(buf ^ 1);
-    __syncthreads();
-  }
+  const uint32_t lds0 = (uint32_t)(uintptr_t)(lds_char*)sm;
+  const lds_char* lds = (const lds_char*)sm;
 
-  // Epilogue.  acc[a][b][r] is channel n0 + wn + 32a + 8(r/4) + 4g2 + r%4 of token
-  // m0 + wm + 32b + l32: written straight from there a lane would store 8 bytes per 2 KiB-apart
-  // row.  Instead each wavefront turns its tile through a private piece of the (now idle) LDS,
-  // 32 tokens x 64 channels of float at a time, and writes whole 128-byte runs of a token row:
-  // 16 lanes x 4 channels.  Bias and residual are added in float before the one rounding.
-  float* epi = reinterpret_cast<float*>(wave < 4 ? &sA[0][0] : &sW[0][0]) + (wave & 3) * (32 * kEpiStride);
+  // All output tiles of one token tile, then of the next: every XCD takes an equal, contiguous run
+  // of that list, and workgroup j of an XCD positions j, j + stride, ... of its run.
+  struct Tile {
+    int64_t m0;
+    int which, n0;
+  };
+  const int64_t total = (int64_t)gm * per_m;
+  const int64_t first = total * xcd / kGemmXcds;
+  const int count = (int)(total * (xcd + 1) / kGemmXcds - first);
+  const int stride = gridDim.x / kGemmXcds;
+  auto tile_at = [&](int seq) {
+    Tile t;
+    const int64_t mt = (first + seq) / per_m;
+    const int nt = (int)((first + seq) - mt * per_m);
+    t.m0 = mt * kEdge;
+    t.which = nt / gn;
+    t.n0 = (nt % gn) * kEdge;
+    return t;
+  };
+  int seq = blockIdx.x / kGemmXcds;
+  if (seq >= count) return;  // uniform for the workgroup, before any barrier
+
+  // Copies: an instruction lands 8 LDS rows; a wavefront owns kRows token rows and W rows.  The
+  // chunk swizzle of rows 8 i .. 8 i + 7 differs from that of the first eight by bit 2 for odd i.
+  // W's LDS row 16 ct + i of a wavefront's run of channels is channel kNT i + ct.
+  const uint32_t k2 = (uint32_t)K * 2;
+  const uint32_t lrow = lane >> 3, lchunk = ((lane & 7) ^ (lane >> 4)) * 16u;
+  // where the next slot of A and of W is fetched from: position in the list, k, first row
+  int a_seq = seq, a_k = 0, w_seq = seq, w_k = 0;
+  const uint16_t *abase, *wbase;
+  uint32_t alast;   // last token row that exists, counted from this wavefront's first
+  int64_t wodd;     // elements from a W row to the one 8 kNT channels on (0 where that does not exist)
+  auto aim_a = [&]() {
+    const int64_t m = tile_at(a_seq).m0 + wave * kRows;
+    alast = (uint32_t)max(min(rows - 1 - m, (int64_t)kRows - 1), (int64_t)0);
+    abase = uniform_ptr(A + min(m, rows - 1) * K);
+  };
+  auto aim_w = [&]() {
+    const Tile t = tile_at(w_seq);
+    const int n = t.n0 + wn;
+    wbase = uniform_ptr(outs.W[t.which] + (int64_t)(min(n, N - 64) + (wave & 3) * (kNT / 4)) * K);
+    wodd = n + 8 * kNT < N ? (int64_t)(8 * kNT) * K : 0;
+  };
+  // token rows past the end repeat the last one, channels past the end others; never stored
+  // (the lane's place is made opaque so that the offsets are worked out here and not held)
+  auto copy_a = [&](int slot) {
+    uint32_t lr = lrow;
+    asm volatile("" : "+v"(lr));
 #pragma unroll
-  for (int b = 0; b < 2; ++b)
-#pragma unroll
-    for (int half = 0; half < 2; ++half) {
-      const int ch = (lane & 15) * 4;                  // channel inside this 64-channel run
-      const int n = n0 + wn + half * 64 + ch;
-      // residual values of the eight rows this lane will finish, requested before the LDS turn
-      u32x2 rr[8];
-#pragma unroll
-      for (int i = 0; i < 8; ++i) {
-        const int64_t m = m0 + wm + b * 32 + i * 4 + (lane >> 4);
-        rr[i] = u32x2{0u, 0u};
-        if (kResidual && m < rows && n < N) rr[i] = *reinterpret_cast<const u32x2*>(R + m * N + n);
-      }
-#pragma unroll
-      for (int a2 = 0; a2 < 2; ++a2)
-#pragma unroll
-        for (int r4 = 0; r4 < 4; ++r4) {
-          const int a = half * 2 + a2;
-          f32x4 v4 = {acc[a][b][r4 * 4 + 0], acc[a][b][r4 * 4 + 1], acc[a][b][r4 * 4 + 2],
-                      acc[a][b][r4 * 4 + 3]};
-          *reinterpret_cast<f32x4*>(epi + l32 * kEpiStride + a2 * 32 + r4 * 8 + g2 * 4) = v4;
-        }
-      f32x4 bv = {0.f, 0.f, 0.f, 0.f};
-      if (bias && n < N) {
-#pragma unroll
-        for (int i = 0; i < 4; ++i) bv[i] = bias[n + i];
-      }
-#pragma unroll
-      for (int i = 0; i < 8; ++i) {
-        const int t = i * 4 + (lane >> 4);             // token inside this 32-token block
-        const int64_t m = m0 + wm + b * 32 + t;
-        f32x4 o = *reinterpret_cast<const f32x4*>(epi + t * kEpiStride + ch);
-        if (m < rows && n < N) {
-          o += bv;
-          if (kResidual) {
-            o[0] += lo16(rr[i][0]);
-            o[1] += hi16(rr[i][0]);
-            o[2] += lo16(rr[i][1]);
-            o[3] += hi16(rr[i][1]);
-          }
-          u32x2 w = {pack2(o[0], o[1]), pack2(o[2], o[3])};
-          *reinterpret_cast<u32x2*>(Y + m * N + n) = w;
-        }
-      }
+    for (int i = 0; i < kCopies; ++i)
+      dma16(abase, __umul24(min(i * 8 + lr, alast), k2) + (lchunk ^ ((i & 1) * 64u)),
+            lds0 + slot * kSlotBytes + (wave * kRows + i * 8) * 128);
+    if (++a_k < nk) {
+      abase += kTK;
+    } else {
+      a_k = 0;
+      a_seq += stride;
+      if (a_seq < count) aim_a();
     }
+  };
+  auto copy_w = [&](int slot) {
+    uint32_t lr = lrow;
+    asm volatile("" : "+v"(lr));
+#pragma unroll
+    for (int i = 0; i < kCopies; ++i)
+      dma16(wbase + (i >> 1) * K + ((i & 1) ? wodd : 0), (__umul24(lr, kNT * k2) + lchunk) ^ ((i & 1) * 64u),
+            lds0 + slot * kSlotBytes + (wave * kRows + i * 8) * 128);
+    if (++w_k < nk) {
+      wbase += kTK;
+    } else {
+      w_k = 0;
+      w_seq += stride;
+      if (w_seq < count) aim_w();
+    }
+  };
+  int slot = 0;                // of this step's A; W's is the next, and so on in turn
+  bool ahead = false;          // the youngest copies are an A that the coming step does not need
+  auto ring = [](int s) { return s >= kSlots ? s - kSlots : s; };
+  // the copies that go out in a step: the next step's W, then the A after the next
+  auto fetch = [&](int at) {
+    if (w_seq < count) copy_w(ring(at + 3));
+    ahead = a_seq < count;
+    if (ahead) copy_a(ring(at + 4));
+  };
+
+  // byte offsets of this lane's fragment chunks inside a slot, for the two 32-wide halves of k
+  const int f0 = c * 128 + ((G ^ ((c >> 1) & 7)) * 16), f1 = f0 ^ 64;
+
+  aim_a();
+  aim_w();
+  copy_a(0);
+  copy_w(1);
+  if (a_seq < count) copy_a(2);
+  wait_vm0();
+  lds_barrier();
+  fetch(0);
+  bool stores_behind = false;  // exactly kTileStores stores are younger than the first step's fetch
+  for (;;) {
+    const Tile cur = tile_at(seq);
+    f32x4 acc[kMT][kNT];  // [token tile][channel tile]
+#pragma unroll
+    for (int t = 0; t < kMT; ++t)
+#pragma unroll
+      for (int a = 0; a < kNT; ++a) acc[t][a] = f32x4{0.f, 0.f, 0.f, 0.f};
+    for (int k = 0; k < nk; ++k) {
+      if (k > 0) {  // (a tile's first step is waited for, and its fetch sent, before the last one's stores)
+        if (!ahead) wait_vm0();
+        else if (k == 1 && stores_behind) wait_vm<kCopies + kTileStores>();
+        else wait_vm<kCopies>();
+        lds_barrier();  // everybody's copies of this step are in, and the last step's slots are free
+        fetch(slot);
+      }
+      const lds_char* at_a = lds + slot * kSlotBytes + wm * 128;
+      const lds_char* at_w = lds + ring(slot + 1) * kSlotBytes + wn * 128;
+#pragma unroll
+      for (int h = 0; h < 2; ++h) {
+        Frag fa[kMT], fw[kNT];
+#pragma unroll
+        for (int a = 0; a < kNT; ++a)
+          fw[a].u = *reinterpret_cast<const __attribute__((address_space(3))) u32x4*>(
+              at_w + (h ? f1 : f0) + a * 16 * 128);
+#pragma unroll
+        for (int t = 0; t < kMT; ++t)
+          fa[t].u = *reinterpret_cast<const __attribute__((address_space(3))) u32x4*>(
+              at_a + (h ? f1 : f0) + t * 16 * 128);
+#pragma unroll
+        for (int t = 0; t < kMT; ++t)
+#pragma unroll
+          for (int a = 0; a < kNT; ++a)
+            acc[t][a] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fa[t].h, fw[a].h, acc[t][a], 0, 0, 0);
+      }
+      slot = ring(slot + 2);
+    }
+
+    // Epilogue: a lane holds channels n .. n + kNT - 1 of token m for every (token tile, r).  What
+    // it reads is waited for together with the next step's operands; then that step's fetch goes
+    // out ahead of the stores, which have two steps to drain before a copy is awaited behind them.
+    // (The lane's place is made opaque here: otherwise its store addresses are worked out before
+    // the loops and held in registers that the products need.)
+    typedef uint32_t Run __attribute__((ext_vector_type(kNT / 2)));  // kNT channels of a token
+    int ec = c, eg = 4 * G;
+    asm("" : "+v"(ec), "+v"(eg));
+    const float* __restrict__ bias = outs.bias[cur.which];
+    const int n = cur.n0 + wn + ec * kNT;
+    const bool channels = n < N;
+    const int64_t corner = (cur.m0 + wm) * N + cur.n0 + wn;  // of this wavefront's part, uniform
+    const int mleft = (int)min(rows - cur.m0 - wm, (int64_t)kEdge) - eg;  // tokens from this lane's first on
+    const uint32_t lane_at = (uint32_t)(eg * N + ec * kNT) * 2u;
+    float bv[kNT];
+    Run rr[kMT][4];
+#pragma unroll
+    for (int a = 0; a < kNT; ++a) bv[a] = (bias && channels) ? bias[n + a] : 0.f;
+    if (kResidual) {
+#pragma unroll
+      for (int t = 0; t < kMT; ++t)
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+          rr[t][r] = Run(0u);
+          if (channels && t * 16 + r < mleft)
+            rr[t][r] = *reinterpret_cast<const Run*>(
+                reinterpret_cast<const char*>(R + corner + (int64_t)(t * 16 + r) * N) + lane_at);
+        }
+    }
+    wait_vm0();
+    const bool more = seq + stride < count;
+    if (more) {
+      lds_barrier();
+      fetch(slot);
+    }
+    auto store = [&](int t, int r) {
+      Run w;
+#pragma unroll
+      for (int i = 0; i < kNT / 2; ++i) {
+        float lo = acc[t][2 * i][r] + bv[2 * i], hi = acc[t][2 * i + 1][r] + bv[2 * i + 1];
+        if (kResidual) {
+          lo += lo16(rr[t][r][i]);
+          hi += hi16(rr[t][r][i]);
+        }
+        w[i] = pack2(lo, hi);
+      }
+      *reinterpret_cast<Run*>(
+          reinterpret_cast<char*>(outs.Y[cur.which] + corner + (int64_t)(t * 16 + r) * N) + lane_at) = w;
+    };
+    const bool full = cur.m0 + kEdge <= rows && cur.n0 + kEdge <= N;
+    if (full) {
+#pragma unroll
+      for (int t = 0; t < kMT; ++t)
+#pragma unroll
+        for (int r = 0; r < 4; ++r) store(t, r);
+    } else {
+#pragma unroll
+      for (int t = 0; t < kMT; ++t)
+#pragma unroll
+        for (int r = 0; r < 4; ++r)
+          if (channels && t * 16 + r < mleft) store(t, r);
+    }
+    if (!more) break;
+    // a partial tile's stores are not counted: its successor waits for everything
+    stores_behind = full;
+    if (!full) ahead = false;
+    seq += stride;
+  }
 }
 
 hipError_t launch_layernorm(const void* x, const float* gamma, const float* beta, void* y,
@@ -298,21 +384,65 @@ hipError_t launch_layernorm(const void* x, const float* gamma, const float* beta
   return hipGetLastError();
 }
 
+template <int kEdge>
+static hipError_t launch_linear_tiles(const uint16_t* A, const LinearOuts& outs, const uint16_t* R,
+                                      int64_t rows, int N, int K, hipStream_t st) {
+  const int64_t gm = (rows + kEdge - 1) / kEdge;
+  const int gn = (N + kEdge - 1) / kEdge;
+  const int64_t per_xcd = (gm * gn * outs.count + kGemmXcds - 1) / kGemmXcds;
+  if (gm > 0x7FFFFFFF || per_xcd > 0x3FFFFFFF) return hipErrorInvalidConfiguration;
+  constexpr int64_t kMost = kEdge == 256 ? kGemmCus : 2 * kGemmCus;  // workgroups resident at once
+  const int64_t groups = per_xcd * kGemmXcds;
+  const dim3 grid((unsigned)(groups < kMost ? groups : kMost));
+  if (R)
+    hipLaunchKernelGGL((linear_kernel<kEdge, true>), grid, dim3(kGemmThreads), 0, st, A, outs, R, rows,
+                       N, K, (int)gm, gn);
+  else
+    hipLaunchKernelGGL((linear_kernel<kEdge, false>), grid, dim3(kGemmThreads), 0, st, A, outs, R, rows,
+                       N, K, (int)gm, gn);
+  return hipGetLastError();
+}
+
+// Times of a launch in microseconds, from what a round of tiles took at K = 1024 (which they
+// follow): 256-wide tiles 33, one to a CU; 128-wide ones 20.6 two to a CU and 14 alone, 7 where a
+// CU's last one runs alone behind others.
+static double linear_time(int64_t rows, int edge, int N, int K, int count) {
+  const int64_t tiles = (rows + edge - 1) / edge * ((N + edge - 1) / edge) * count;
+  const int64_t mine = (tiles + kGemmXcds - 1) / kGemmXcds;  // of one XCD, which has 32 CUs
+  const double k = K / 1024.0;
+  if (edge == 256) return k * 33.0 * ((mine + 31) / 32);
+  const int64_t full = mine / 64, rest = mine % 64;
+  return k * (20.6 * full + (rest == 0 ? 0.0 : rest > 32 ? 20.6 : full ? 7.0 : 14.0));
+}
+
 hipError_t launch_linear(const void* A, const LinearOuts& outs, const void* R, int64_t rows, int N,
                          int K, hipStream_t st) {
-  if (K % kTK != 0 || N % 8 != 0 || outs.count < 1 || outs.count > 3) return hipErrorInvalidValue;
-  const int64_t gm = (rows + kTM - 1) / kTM;
-  const int gn = (N + kTN - 1) / kTN;
-  const int64_t groups = (gm + kGemmXcds - 1) / kGemmXcds * kGemmXcds * gn * outs.count;
-  if (groups > 0x7FFFFFFF) return hipErrorInvalidConfiguration;
+  if (K % 64 != 0 || N % 64 != 0 || outs.count < 1 || outs.count > 3) return hipErrorInvalidValue;
   (void)hipGetLastError();
-  if (R)
-    hipLaunchKernelGGL(linear_kernel<true>, dim3((unsigned)groups), dim3(kGemmThreads), 0, st,
-                       (const uint16_t*)A, outs, (const uint16_t*)R, rows, N, K, (int)gm, gn);
-  else
-    hipLaunchKernelGGL(linear_kernel<false>, dim3((unsigned)groups), dim3(kGemmThreads), 0, st,
-                       (const uint16_t*)A, outs, (const uint16_t*)R, rows, N, K, (int)gm, gn);
-  return hipGetLastError();
+  // Large tiles move half the bytes per product, small ones fill the chip and its last round: the
+  // rows of whole rounds of large tiles go to them and the others to small tiles, if that is at
+  // least 6 % ahead of large tiles alone (a second launch costs 4 us).  Measured for the Q/K/V and
+  // the output projection at C = 1024, large / small / chosen, us: 522 rows 30 + 29 / 15 + 13 / 14 + 14;
+  // 5 496 rows 58 + 32 / 46 + 20 / 45 + 21; 10 992 rows 90 + 35 / 85 + 32 / 82 + 31; 32 976 rows
+  // 232 + 110 / 270 + 104 / 229 + 105; 137 400 rows 817 + 325 / 1022 + 374 / large.
+  const int64_t per_m = (int64_t)((N + 255) / 256) * outs.count;
+  const int64_t gm = (rows + 255) / 256;
+  const int64_t whole = gm * per_m / kGemmCus * kGemmCus / per_m;  // token tiles that fill whole rounds
+  const int64_t split = whole * 256 < rows ? whole * 256 : 0;
+  const double large = linear_time(rows, 256, N, K, outs.count);
+  const double small = linear_time(rows, 128, N, K, outs.count);
+  const double both = split ? linear_time(split, 256, N, K, outs.count) +
+                                  linear_time(rows - split, 128, N, K, outs.count) + 4.0
+                            : large;
+  const uint16_t* a = (const uint16_t*)A;
+  const uint16_t* r = (const uint16_t*)R;
+  if (small < 0.97 * large && small <= both) return launch_linear_tiles<128>(a, outs, r, rows, N, K, st);
+  if (both >= 0.94 * large) return launch_linear_tiles<256>(a, outs, r, rows, N, K, st);
+  const hipError_t e = launch_linear_tiles<256>(a, outs, r, split, N, K, st);
+  if (e != hipSuccess) return e;
+  LinearOuts rest = outs;
+  for (int i = 0; i < outs.count; ++i) rest.Y[i] += split * N;
+  return launch_linear_tiles<128>(a + split * K, rest, r ? r + split * N : nullptr, rows - split, N, K, st);
 }
 
 }  // namespace agg

@@ -66,3 +66,44 @@ def test_narrow_tail_per_frame(L):
     want_o, want_lse = orc.frame_rows(oshape(shape), qb, kb, vb, rows)
     got_lse = lse.permute(1, 0, 2).reshape(1, 16, shape.NQ)
     check_output(O, got_lse, want_o, want_lse, rows, "frame tail %d" % L, q, k, shape.scale)
+
+
+def _bf16(t):
+    return t.to(torch.bfloat16).double()
+
+
+# (heads, rows): which tiles a projection takes depends on both (launch_linear)
+PROJECTIONS = [
+    (1, 3), (1, 129),   # one k step, one and two small tiles of tokens
+    (1, 30000),         # one k step and several small tiles per workgroup
+    (3, 999),           # 192 channels: the last small tile of every matrix is half empty
+    (4, 66048),         # large tiles, several per workgroup, all whole
+    (5, 261),           # 320 channels
+    (16, 21999),        # whole rounds of large tiles, the other rows in small ones
+    (33, 30000),        # 2112 channels: the last large tile of every matrix is a quarter full
+]
+
+
+@pytest.mark.parametrize("H,rows", PROJECTIONS)
+def test_projection_tiles(H, rows):
+    """Projections at the sizes where their tiles change, in a block of three-token frames (their
+    attention is three columns) against float64 with the five bf16 roundings that the interface
+    states.  Bounds: those of test_global_block."""
+    C, L = 64 * H, 3
+    shape = agg.make_shape(1, rows // L, 1, L, 0, H, 64, 1, 1, 0)
+    assert shape.NQ == rows
+    wts = inputs.block_weights(C, seed=rows + H, device="cuda")
+    x = inputs.block_input(1, rows, C, seed=rows + H, device="cuda")
+    y, _ = harness.block_forward(shape, agg.AGG_BLOCK_FRAME, wts, x)
+    x64 = x.double().view(rows, C)
+    ln = _bf16(torch.nn.functional.layer_norm(x64, (C,), wts["ln_gamma"].double(),
+                                              wts["ln_beta"].double(), wts["ln_eps"]))
+    q, k, v = (_bf16(ln @ wts["w_" + n].double().t().contiguous() + wts["b_" + n].double())
+               .view(rows // L, L, H, 64).permute(0, 2, 1, 3).contiguous() for n in "qkv")
+    s = (q[:, :, :, None, :] * k[:, :, None, :, :]).sum(-1) * 0.125
+    o = _bf16((torch.softmax(s, -1)[..., None] * v[:, :, None, :, :]).sum(3))
+    o = o.permute(0, 2, 1, 3).reshape(rows, C)
+    want = _bf16(x64 + o @ wts["w_o"].double().t().contiguous() + wts["b_o"].double())
+    err = (y.double().view(rows, C) - want).abs()
+    assert bool(torch.isfinite(y).all())
+    assert float(err.max()) <= 6e-2 and float(err.mean()) <= 4e-3, (float(err.max()), float(err.mean()))

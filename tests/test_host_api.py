@@ -276,3 +276,31 @@ def test_attention_kernel_leaves_m0_to_its_copy_statements(tmp_path):
             offenders.append(line.strip())
     assert seen_copy >= 4, "the copy statements were not found"
     assert not offenders, offenders[:5]
+
+
+def test_projection_kernels_leave_m0_to_their_copy_statements(tmp_path):
+    """The same for the projection kernels, which use the same copy statement; and their waits
+    count on no scratch access between the copies: none of them may spill."""
+    import subprocess
+
+    from paper_2512_02541_amd import build as b
+
+    out = tmp_path / "agg_block.s"
+    cmd = [b.HIPCC, *b.FLAGS, "-I", os.path.join(ROOT, "include"), "-I", b.CSRC, "-S",
+           "--cuda-device-only", os.path.join(b.CSRC, "agg_block.hip"), "-o", str(out)]
+    subprocess.check_call(cmd, stderr=subprocess.DEVNULL)
+    text = out.read_text()
+    inside, seen_copy, offenders = False, 0, []
+    for line in text.splitlines():
+        code = line.split(";")[0] if not line.lstrip().startswith(";;#") else line
+        if "#ASMSTART" in line:
+            inside = True
+        elif "#ASMEND" in line:
+            inside = False
+        elif inside:
+            seen_copy += "global_load_lds_dwordx4" in code
+        elif re.search(r"\bm0\b", code):
+            offenders.append(line.strip())
+    assert seen_copy >= 16, "the copy statements were not found"
+    assert not offenders, offenders[:5]
+    assert "scratch_load" not in text and "scratch_store" not in text
