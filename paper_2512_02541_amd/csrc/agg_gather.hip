@@ -111,30 +111,55 @@ __device__ inline void gather_tile(const Geom& g, const uint16_t* __restrict__ K
   }
   __syncthreads();
 
-  // stage 1: 16-byte chunks, (row, head, j) with j the fastest index
-  const int chunks = kTileRows * nheads * 8;
-  for (int c = tid; c < chunks; c += kSubThreads) {
-    int j = c & 7;
-    int hl = (c >> 3) % nheads;
-    int row = (c >> 3) / nheads;
-    int64_t tok = s.tok[row];
-    u32x4 kv = {0u, 0u, 0u, 0u}, vv = {0u, 0u, 0u, 0u};
-    if (tok >= 0) {
-      int64_t off = (((int64_t)b * g.NQ + tok) * g.H + (h0 + hl)) * kHeadDim + j * 8;
-      if (kPool && s.win[row] != ((1 << 8) | 1)) {
-        const int wrows = s.win[row] >> 8, wcols = s.win[row] & 255;
-        const int64_t cell = (int64_t)g.H * kHeadDim;  // elements between neighbouring tokens
-        kv = window_mean(K, off, cell * g.n_w, cell, wrows, wcols);
-        vv = window_mean(V, off, cell * g.n_w, cell, wrows, wcols);
-      } else {
-        kv = *reinterpret_cast<const u32x4*>(K + off);
-        vv = *reinterpret_cast<const u32x4*>(V + off);
-      }
-    }
-    // K: chunk j covers channels 8j..8j+7 -> slot (((row/32)*4 + j/2)*2 + j%2)*32 + row%32
-    int kslot = (((row >> 5) * 4 + (j >> 1)) * 2 + (j & 1)) * 32 + (row & 31);
+  // stage 1: 16-byte chunks, (row, head, j) with j the fastest index.  K's chunk j covers
+  // channels 8j..8j+7 -> slot (((row/32)*4 + j/2)*2 + j%2)*32 + row%32
+  auto keep = [&](int row, int hl, int j, u32x4 kv, u32x4 vv) {
+    const int kslot = (((row >> 5) * 4 + (j >> 1)) * 2 + (j & 1)) * 32 + (row & 31);
     *reinterpret_cast<u32x4*>(&s.k[hl][k_lds_pos(kslot, hl) * 8]) = kv;
     *reinterpret_cast<u32x4*>(&s.v[hl * kVHead + row * kVPad + j * 8]) = vv;
+  };
+  if (!kPool && nheads == kHeadGroup) {
+    // all of a thread's reads before any of them is used
+    constexpr int kReads = kTileRows * kHeadGroup * 8 / kSubThreads;
+    u32x4 kv[kReads], vv[kReads];
+#pragma unroll
+    for (int i = 0; i < kReads; ++i) {
+      const int c = tid + i * kSubThreads, j = c & 7, hl = (c >> 3) % kHeadGroup;
+      const int64_t tok = s.tok[(c >> 3) / kHeadGroup];
+      kv[i] = vv[i] = u32x4{0u, 0u, 0u, 0u};
+      if (tok >= 0) {
+        const int64_t off = (((int64_t)b * g.NQ + tok) * g.H + (h0 + hl)) * kHeadDim + j * 8;
+        kv[i] = *reinterpret_cast<const u32x4*>(K + off);
+        vv[i] = *reinterpret_cast<const u32x4*>(V + off);
+      }
+    }
+#pragma unroll
+    for (int i = 0; i < kReads; ++i) {
+      const int c = tid + i * kSubThreads;
+      keep((c >> 3) / kHeadGroup, (c >> 3) % kHeadGroup, c & 7, kv[i], vv[i]);
+    }
+  } else {
+    const int chunks = kTileRows * nheads * 8;
+    for (int c = tid; c < chunks; c += kSubThreads) {
+      int j = c & 7;
+      int hl = (c >> 3) % nheads;
+      int row = (c >> 3) / nheads;
+      int64_t tok = s.tok[row];
+      u32x4 kv = {0u, 0u, 0u, 0u}, vv = {0u, 0u, 0u, 0u};
+      if (tok >= 0) {
+        int64_t off = (((int64_t)b * g.NQ + tok) * g.H + (h0 + hl)) * kHeadDim + j * 8;
+        if (kPool && s.win[row] != ((1 << 8) | 1)) {
+          const int wrows = s.win[row] >> 8, wcols = s.win[row] & 255;
+          const int64_t cell = (int64_t)g.H * kHeadDim;  // elements between neighbouring tokens
+          kv = window_mean(K, off, cell * g.n_w, cell, wrows, wcols);
+          vv = window_mean(V, off, cell * g.n_w, cell, wrows, wcols);
+        } else {
+          kv = *reinterpret_cast<const u32x4*>(K + off);
+          vv = *reinterpret_cast<const u32x4*>(V + off);
+        }
+      }
+      keep(row, hl, j, kv, vv);
+    }
   }
   __syncthreads();
 
@@ -176,7 +201,7 @@ constexpr int kMeanBatch = 256;       // token ids resolved per pass through LDS
 constexpr int kMeanMaxChunks = 4096;  // upper bound on partials per batch element
 
 struct MeanLds {
-  float red[kSubThreads][17];
+  float red[kSubThreads][17];  // per thread: eight channels of K, eight of V
   int32_t tok[kMeanBatch];
   int32_t wcnt[kSubThreads / 64];
 };
@@ -187,7 +212,7 @@ struct MeanPlan {
   int rows_per_chunk;  // dropped rows per partial
   int cpr_b;           // 16-byte chunks of a row handled by one workgroup (<= 256)
   int rpp;             // rows in flight per pass = 256 / cpr_b
-  int ncolblk;         // workgroups side by side to cover a row (1 unless H > 32)
+  int ncolblk;         // workgroups side by side to cover a row
 };
 
 static MeanPlan mean_plan(const Geom& g) {
@@ -200,10 +225,19 @@ static MeanPlan mean_plan(const Geom& g) {
   int64_t rows = (g.n_dropped + kMeanMaxChunks - 1) / kMeanMaxChunks;
   p.rows_per_chunk = (int)(rows < kMinRowsPerChunk ? kMinRowsPerChunk : rows);
   p.nchunks = (int)((g.n_dropped + p.rows_per_chunk - 1) / p.rows_per_chunk);
-  const int cpr = g.H * kHeadDim / 8;
-  p.cpr_b = cpr < kSubThreads ? cpr : kSubThreads;
+  // Few partials: the rows of one are shared out by heads to several workgroups, down to one head
+  // (128 bytes of a row) each, until kMeanFill workgroups are at work.  The partials and their
+  // number stay as they are.  With whole rows a workgroup's 512 of them, two at a time, took 40 us
+  // however short the sequence.  The call, us, whole rows / 256 / 512 / 1024 workgroups: 2 frames of
+  // 37x37 44 / 12 / 12 / 12; 10 frames 46 / 18.5 / 18.5 / 18.5; 20 frames 67 / 30 / 33 / 33; 40 frames
+  // 75 / 57 / 59 / 64; 100 frames 176 / 170 / 173 / 174; 300 frames 443 / 427 (not split).
+  constexpr int kMeanFill = 256;
+  int heads = g.H < kSubThreads / 8 ? g.H : kSubThreads / 8;
+  while (heads > 1 && (int64_t)p.nchunks * ((g.H + heads - 1) / heads) * g.B < kMeanFill)
+    heads = (heads + 1) / 2;
+  p.cpr_b = heads * 8;
   p.rpp = kSubThreads / p.cpr_b;
-  p.ncolblk = (cpr + kSubThreads - 1) / kSubThreads;
+  p.ncolblk = (g.H + heads - 1) / heads;
   return p;
 }
 
@@ -248,10 +282,15 @@ __device__ inline void add_rows(const MeanLds& s, int n, int rl, int rpp, int C,
 }
 
 // Combines the row lanes in ascending order (fixed order -> reproducible) and writes the
-// workgroup's partial sums.
+// workgroup's partial sums; with `mean` given (a single partial: nothing is left to add) the
+// means themselves, for `n_rows` rows.  One value per thread and turn.
+struct MeanOut {
+  float *k, *v;  // [B, C]
+  int64_t n_rows;
+};
 __device__ inline void write_partial(MeanLds& s, const float (&ak)[8], const float (&av)[8],
                                      float* __restrict__ partial, const MeanPlan& p, int chunk,
-                                     int b, int rl, int cg, int col, int C) {
+                                     int colblk, int b, int C, const MeanOut* mean = nullptr) {
   const int tid = threadIdx.x;
 #pragma unroll
   for (int i = 0; i < 8; ++i) {
@@ -259,25 +298,16 @@ __device__ inline void write_partial(MeanLds& s, const float (&ak)[8], const flo
     s.red[tid][8 + i] = av[i];
   }
   __syncthreads();
-  if (rl == 0 && col < C) {
-    float sk[8], sv[8];
-#pragma unroll
-    for (int i = 0; i < 8; ++i) sk[i] = sv[i] = 0.f;
-    for (int r = 0; r < p.rpp; ++r) {
-      int t = r * p.cpr_b + cg;
-#pragma unroll
-      for (int i = 0; i < 8; ++i) {
-        sk[i] += s.red[t][i];
-        sv[i] += s.red[t][8 + i];
-      }
-    }
-    float* pk = partial + (((int64_t)b * p.nchunks + chunk) * 2 + 0) * C + col;
-    float* pv = partial + (((int64_t)b * p.nchunks + chunk) * 2 + 1) * C + col;
-#pragma unroll
-    for (int i = 0; i < 8; ++i) {
-      pk[i] = sk[i];
-      pv[i] = sv[i];
-    }
+  const int ncol = p.cpr_b * 8;
+  for (int v = tid; v < 2 * ncol; v += kSubThreads) {
+    const int which = v >= ncol, c = v - which * ncol, col = colblk * ncol + c;
+    if (col >= C) continue;
+    float sum = 0.f;
+    for (int r = 0; r < p.rpp; ++r) sum += s.red[r * p.cpr_b + (c >> 3)][8 * which + (c & 7)];
+    if (mean)
+      (which ? mean->v : mean->k)[(int64_t)b * C + col] = (float)((double)sum / (double)mean->n_rows);
+    else
+      partial[(((int64_t)b * p.nchunks + chunk) * 2 + which) * C + col] = sum;
   }
 }
 
@@ -286,12 +316,13 @@ __device__ inline void write_partial(MeanLds& s, const float (&ak)[8], const flo
 // of one per load).
 __device__ inline void mean_partial(const Geom& g, const uint16_t* __restrict__ K,
                                     const uint16_t* __restrict__ V, float* __restrict__ partial,
-                                    const MeanPlan& p, int chunk, int colblk, int b, MeanLds& s) {
+                                    const MeanPlan& p, int chunk, int colblk, int b,
+                                    const MeanOut& mean, MeanLds& s) {
   const int tid = threadIdx.x;
   const int C = g.H * kHeadDim;
   const int cg = tid % p.cpr_b;                        // 16-byte chunk inside this channel block
   const int rl = tid / p.cpr_b;                        // row lane
-  const int col = (colblk * kSubThreads + cg) * 8;     // first channel of this thread
+  const int col = (colblk * p.cpr_b + cg) * 8;         // first channel of this thread
   const bool active = (rl < p.rpp) && (col < C);
   const uint16_t* Kb = K + (int64_t)b * g.NQ * C + col;
   const uint16_t* Vb = V + (int64_t)b * g.NQ * C + col;
@@ -309,7 +340,7 @@ __device__ inline void mean_partial(const Geom& g, const uint16_t* __restrict__ 
     __syncthreads();
     if (active) add_rows(s, n, rl, p.rpp, C, Kb, Vb, ak, av);
   }
-  write_partial(s, ak, av, partial, p, chunk, b, rl, cg, col, C);
+  write_partial(s, ak, av, partial, p, chunk, colblk, b, C, p.nchunks == 1 ? &mean : nullptr);
 }
 
 // Mean role for a caller's list: the run is a range of token ids; a token is summed when it is
@@ -326,7 +357,7 @@ __device__ inline void mean_partial_bits(const Geom& g, const uint16_t* __restri
   const int C = g.H * kHeadDim;
   const int cg = tid % p.cpr_b;
   const int rl = tid / p.cpr_b;
-  const int col = (colblk * kSubThreads + cg) * 8;
+  const int col = (colblk * p.cpr_b + cg) * 8;
   const bool active = (rl < p.rpp) && (col < C);
   const uint16_t* Kb = K + (int64_t)b * g.NQ * C + col;
   const uint16_t* Vb = V + (int64_t)b * g.NQ * C + col;
@@ -362,7 +393,7 @@ __device__ inline void mean_partial_bits(const Geom& g, const uint16_t* __restri
     if (active) add_rows(s, n, rl, p.rpp, C, Kb, Vb, ak, av);
   }
   if (tid == 0 && colblk == 0) cnt[(int64_t)b * p.nchunks + chunk] = total;
-  write_partial(s, ak, av, partial, p, chunk, b, rl, cg, col, C);
+  write_partial(s, ak, av, partial, p, chunk, colblk, b, C);
 }
 
 union SubLds {
@@ -375,13 +406,15 @@ union SubLds {
 __global__ __launch_bounds__(kSubThreads) void subsample_kernel(
     Geom g, const uint16_t* __restrict__ K, const uint16_t* __restrict__ V,
     uint16_t* __restrict__ Kc, uint16_t* __restrict__ Vc, int32_t* __restrict__ idx,
-    float* __restrict__ partial, MeanPlan plan, int n_mean, int n_gather, int nhg) {
+    float* __restrict__ partial, MeanPlan plan, int n_mean, int n_gather, int nhg,
+    float* __restrict__ kmean, float* __restrict__ vmean) {
   __shared__ __align__(16) SubLds lds;
   const int per_b = n_mean + n_gather;
   const int b = blockIdx.x / per_b;
   const int r = blockIdx.x % per_b;
   if (r < n_mean) {
-    mean_partial(g, K, V, partial, plan, r / plan.ncolblk, r % plan.ncolblk, b, lds.mean);
+    mean_partial(g, K, V, partial, plan, r / plan.ncolblk, r % plan.ncolblk, b,
+                 MeanOut{kmean, vmean, g.n_dropped}, lds.mean);
   } else {
     const int rr = r - n_mean;
     gather_tile(g, K, V, Kc, Vc, idx, nullptr, rr / nhg, rr % nhg, b, lds.gather);
@@ -412,14 +445,17 @@ __global__ __launch_bounds__(kFinalCols * kFinalGroups) void mean_final_kernel(
     for (int k = rg; k < nchunks; k += kFinalGroups) s += (double)p[(int64_t)k * 2 * C];
   }
   red[rg][cl] = s;
-  if (threadIdx.x == 0) {
+  if (threadIdx.x < 64) {  // the first wavefront adds the counts
     int64_t nd = g.n_dropped;
     if (cnt) {
-      nd = 0;
-      for (int k = 0; k < nchunks; ++k) nd += cnt[(int64_t)b * nchunks + k];
-      if (blockIdx.x == 0) nd_out[b] = (int32_t)nd;
+      int32_t mine = 0;  // (the total is at most N*L < 2^31)
+      for (int k = threadIdx.x; k < nchunks; k += 64) mine += cnt[(int64_t)b * nchunks + k];
+#pragma unroll
+      for (int off = 32; off >= 1; off >>= 1) mine += __shfl_xor(mine, off);
+      nd = mine;
+      if (blockIdx.x == 0 && threadIdx.x == 0) nd_out[b] = mine;
     }
-    nd_s = nd;
+    if (threadIdx.x == 0) nd_s = nd;
   }
   __syncthreads();
   if (rg == 0 && c < 2 * C) {
@@ -461,9 +497,9 @@ hipError_t launch_subsample(const Geom& g, const void* K, const void* V, void* K
   if (groups > 0)
     hipLaunchKernelGGL(subsample_kernel, dim3((unsigned)groups), dim3(kSubThreads), 0, st, g,
                        (const uint16_t*)K, (const uint16_t*)V, (uint16_t*)Kc, (uint16_t*)Vc, idx,
-                       (float*)workspace, plan, (int)n_mean, (int)n_gather, nhg);
+                       (float*)workspace, plan, (int)n_mean, (int)n_gather, nhg, kmean, vmean);
   hipError_t e = hipGetLastError();
-  if (e != hipSuccess || !want_mean) return e;
+  if (e != hipSuccess || !want_mean || plan.nchunks == 1) return e;  // (one partial is the sum)
   const int C = g.H * kHeadDim;
   dim3 grid2((unsigned)((2 * C + kFinalCols - 1) / kFinalCols), (unsigned)g.B);
   hipLaunchKernelGGL(mean_final_kernel, grid2, dim3(kFinalCols * kFinalGroups), 0, st, g,

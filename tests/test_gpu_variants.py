@@ -7,7 +7,7 @@ import torch
 from oracle import sga_oracle as orc
 from paper_2512_02541_amd import binding as agg
 from paper_2512_02541_amd import harness, inputs
-from test_gpu_parity import _idx_case, check_output, oshape, run_case
+from test_gpu_parity import _idx_case, check_output, check_subsample, oshape, run_case
 
 pytestmark = pytest.mark.gpu
 
@@ -107,3 +107,23 @@ def test_projection_tiles(H, rows):
     err = (y.double().view(rows, C) - want).abs()
     assert bool(torch.isfinite(y).all())
     assert float(err.max()) <= 6e-2 and float(err.mean()) <= 4e-3, (float(err.max()), float(err.mean()))
+
+
+@pytest.mark.parametrize("H", [1, 3, 16, 33])
+@pytest.mark.parametrize("B,nq", [(1, 1024), (2, 1026), (1, 70000)])
+def test_mean_split_by_heads(H, B, nq):
+    """Few partial sums: their rows are shared out by heads.  512 dropped rows are one partial, whose
+    workgroups write the means themselves; 513 are two; 35 000 are enough partials that a workgroup
+    takes several heads (and at 33 heads the last one fewer)."""
+    if nq > 10000 and H == 33:
+        nq = 35000
+    shape = agg.make_shape(B, 1, 1, nq, 0, H, 64, 1, 2, 0)
+    q, k, v = inputs.iid_qkv(B, nq, H, 64, seed=8100 + nq + H, device="cuda")
+    buf = harness.alloc(shape, "cuda", poison=True)
+    harness.subsample(buf, k, v)
+    again = harness.alloc(shape, "cuda", poison=True)
+    agg.agg_kv_subsample(shape, k, v, None, None, again.idx, again.kmean, again.vmean,
+                         again.workspace, again.workspace.numel())
+    torch.cuda.synchronize()
+    check_subsample(shape, buf, inputs.bf16_bits(k), inputs.bf16_bits(v))
+    assert torch.equal(buf.kmean, again.kmean) and torch.equal(buf.vmean, again.vmean)
