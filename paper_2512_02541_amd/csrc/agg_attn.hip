@@ -694,8 +694,11 @@ __device__ __forceinline__ bool attend(const AttnArgs& p, int b, int h, int64_t 
   float l_self[kQB][kJ], l_mean[kQB][kJ];  // base-2 logits of the extras (-inf when absent)
   // caller's list: membership comes from a bitmap, the dropped count from device memory
   const int64_t n_drop = p.nd_dev ? (int64_t)p.nd_dev[b] : g.n_dropped;
-  const bool use_mean = (p.flags & AGG_MEAN) && n_drop > 0;
-  const bool use_diag = (p.flags & AGG_DIAG) && (p.kept_bits != nullptr || n_drop > 0);
+  // ordinary and per-frame attention have no extras; where that is known at compile time the fast
+  // path's code is a third shorter (the general path's would spill)
+  constexpr bool kExtras = kSrc != kSrcRows || kGen;
+  const bool use_mean = kExtras && (p.flags & AGG_MEAN) && n_drop > 0;
+  const bool use_diag = kExtras && (p.flags & AGG_DIAG) && (p.kept_bits != nullptr || n_drop > 0);
   const uint32_t* kbits = p.kept_bits ? p.kept_bits + (int64_t)b * ((g.NQ + 31) / 32) : nullptr;
   const int64_t q_wave = q_begin + wave * kWaveQ;
   // first element of query (qb, j, c)'s row of this head in Q, K, V and O

@@ -85,13 +85,15 @@ __host__ __device__ inline int64_t dropped_to_token(const Geom& g, int64_t u) {
 
 // 1 when token `tok` is a patch that is not in the kept set.
 __host__ __device__ inline int token_is_dropped(const Geom& g, int64_t tok) {
-  int64_t frame = tok / g.L;
-  int32_t slot = (int32_t)(tok % g.L);
+  // tok < N*L < 2^31: 32-bit division (much cheaper on the GPU than 64-bit)
+  const uint32_t t = (uint32_t)tok;
+  const uint32_t frame = t / (uint32_t)g.L;
+  const int32_t slot = (int32_t)(t % (uint32_t)g.L);
   if (slot < g.P) return 0;
   if (frame == 0 && g.keep_first) return 0;
-  int32_t p = slot - g.P;
-  int32_t row = p / g.n_w, col = p % g.n_w;
-  return (row % g.s_h != 0) || (col % g.s_w != 0);
+  const uint32_t p = (uint32_t)(slot - g.P);
+  const uint32_t row = p / (uint32_t)g.n_w, col = p % (uint32_t)g.n_w;
+  return (row % (uint32_t)g.s_h != 0) || (col % (uint32_t)g.s_w != 0);
 }
 
 // Element offsets of (row m, channel d) inside one (batch, head) block of the
