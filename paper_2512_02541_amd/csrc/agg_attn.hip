@@ -52,6 +52,8 @@
 //     lazily: a unit's row sums show when a score exceeds it by more than 2^100; only then
 //     (a rare, wavefront-uniform branch) is the unit's maximum taken, the accumulator
 //     rescaled and the unit redone.  No running maximum is computed otherwise.
+//   * A launch with at most one workgroup per CU runs eight wavefronts in each: two groups of four
+//     that take half the key tiles each and add their sums and accumulators at the end (attend).
 //   * The zero-padded rows of the last tile are masked there (the last tile is
 //     peeled), nowhere else.
 //   * The extras enter as the initial state (sum, accumulator) of either path, so
@@ -571,7 +573,9 @@ __device__ __forceinline__ void tile_steps(Wave<kQB, kJ>& w, const u32x4* __rest
 // The key loop of one path.  `first_tile` runs once tile 0 is resident and its first K fragments
 // are loaded (the general path takes its reference there).  Returns false when the fast path
 // found a row sum it cannot trust.
-template <int kSrc, bool kGen, int kQB, int kJ, class FirstTile>
+// kSplit: the workgroup's other wavefronts walk other tiles, perhaps one fewer: no early check, whose
+// barriers would not match (the sums are looked at when the loops are done).
+template <int kSrc, bool kGen, bool kSplit, int kQB, int kJ, class FirstTile>
 __device__ __forceinline__ bool key_loop(Wave<kQB, kJ>& w, u32x4* __restrict__ lds, const KvSource& src,
                                          int ntiles, int last_valid, int tid, int wave,
                                          const FragAddr& fa, int G, FirstTile&& first_tile) {
@@ -610,7 +614,7 @@ __device__ __forceinline__ bool key_loop(Wave<kQB, kJ>& w, u32x4* __restrict__ l
     AGG_TILE(1)
     AGG_TILE(2)
 #undef AGG_TILE
-    if (!kGen && (round & 7) == 7) {  // an overflowing row ends the fast pass early
+    if (!kGen && !kSplit && (round & 7) == 7) {  // an overflowing row ends the fast pass early
       bool bad = false;
 #pragma unroll
       for (int qb = 0; qb < kQB; ++qb)
@@ -634,6 +638,7 @@ __device__ __forceinline__ bool key_loop(Wave<kQB, kJ>& w, u32x4* __restrict__ l
 // then all tails (1).
 struct TilePlan {
   int n_full, n_tail, tail_q, tails_last;
+  int split;  // all workgroups are narrow ones of eight wavefronts that share their keys
 };
 
 // Kernel arguments.
@@ -653,40 +658,55 @@ struct AttnArgs {
   int64_t list_stride;   // 0 when every batch element uses the same list
 };
 
-__shared__ __align__(16) uint16_t smem[2 * kLdsTiles * kTileElems];  // K tiles, then V tiles
+constexpr int kTileLds = 2 * kLdsTiles * kTileElems;  // elements: K tiles, then V tiles
 
-// One workgroup's queries q_begin .. q_end - 1 (at most what its wavefronts hold) by one of the
+// One workgroup's queries q_begin .. q_end - 1 (at most what four wavefronts hold) by one of the
 // two paths.  Returns false, without storing anything, when the fast path met a row it cannot
 // handle.
-template <int kSrc, bool kGen, int kQB, int kJ>
-__device__ __forceinline__ bool attend(const AttnArgs& p, int b, int h, int64_t q_begin,
-                                       int64_t q_end) {
+// tiles: kTileLds elements of LDS per four wavefronts.
+// kSplit (fast path): eight wavefronts; the first four take the extras and the first half of the
+// key tiles, the others the second half.  Without a reference the two halves' sums and accumulators
+// just add: the second group's go through LDS to the first, which finishes the rows.
+template <int kSrc, bool kGen, int kQB, int kJ, bool kSplit = false>
+__device__ __forceinline__ bool attend(const AttnArgs& p, uint16_t* tiles, int b, int h,
+                                       int64_t q_begin, int64_t q_end) {
+  static_assert(!(kGen && kSplit), "the general path's halves would need a common reference");
   constexpr int kWaveQ = wave_queries(kQB, kJ);
   const Geom& g = p.g;
+  const int group = kSplit ? __builtin_amdgcn_readfirstlane((int)threadIdx.x / kAttnThreads) : 0;
+  uint16_t* smem = tiles + group * kTileLds;
   u32x4* lds = reinterpret_cast<u32x4*>(smem);
-  const int tid = threadIdx.x;
+  const int tid = threadIdx.x - group * kAttnThreads;
   const int lane = tid & 63;
   const int wave = tid >> 6;
   const int c = lane & 15;
   const int G = lane >> 4;
   const FragAddr fa = frag_addr(lane);
 
-  const int ntiles = (int)(g.M_pad / kTileRows);
-  const int last_valid = (int)(g.M - (int64_t)(ntiles - 1) * kTileRows);  // 1..64
+  // this group's key tiles: first_tile_no .. first_tile_no + ntiles - 1
+  const int all_tiles = (int)(g.M_pad / kTileRows);
+  const int half = kSplit ? (all_tiles + 1) / 2 : all_tiles;
+  const int skip = group ? half : 0;
+  const int ntiles = group ? all_tiles - half : half;
+  const int64_t rows_here = min(g.M - (int64_t)skip * kTileRows, (int64_t)ntiles * kTileRows);
+  const int last_valid = (int)(rows_here - (int64_t)(ntiles - 1) * kTileRows);  // 1..64
   KvSource src;
-  src.rows = g.M;
+  src.rows = rows_here;
   src.row_bytes = (uint32_t)g.H * (kHeadDim * 2);
   src.max_token = (uint32_t)(g.NQ - 1);
   if (kSrc == kSrcCompact) {
-    const int64_t bh_off = ((int64_t)b * g.H + h) * g.M_pad * kHeadDim;
+    const int64_t bh_off = (((int64_t)b * g.H + h) * g.M_pad + (int64_t)skip * kTileRows) * kHeadDim;
     src.k = uniform_ptr(p.Kc + bh_off);
     src.v = uniform_ptr(p.Vc + bh_off);
     src.list = nullptr;
   } else {
-    const int64_t bh_off = ((int64_t)b * g.NQ * g.H + h) * kHeadDim;
+    const int64_t first_row = (int64_t)b * g.NQ + (kSrc == kSrcRows ? (int64_t)skip * kTileRows : 0);
+    const int64_t bh_off = (first_row * g.H + h) * kHeadDim;
     src.k = uniform_ptr(p.K + bh_off);
     src.v = uniform_ptr(p.V + bh_off);
-    src.list = kSrc == kSrcIndexed ? p.list + (int64_t)b * p.list_stride : nullptr;
+    src.list = kSrc == kSrcIndexed
+                   ? p.list + (int64_t)b * p.list_stride + (int64_t)skip * kTileRows
+                   : nullptr;
   }
 
   Wave<kQB, kJ> w;
@@ -697,8 +717,8 @@ __device__ __forceinline__ bool attend(const AttnArgs& p, int b, int h, int64_t 
   // ordinary and per-frame attention have no extras; where that is known at compile time the fast
   // path's code is a third shorter (the general path's would spill)
   constexpr bool kExtras = kSrc != kSrcRows || kGen;
-  const bool use_mean = kExtras && (p.flags & AGG_MEAN) && n_drop > 0;
-  const bool use_diag = kExtras && (p.flags & AGG_DIAG) && (p.kept_bits != nullptr || n_drop > 0);
+  const bool use_mean = kExtras && group == 0 && (p.flags & AGG_MEAN) && n_drop > 0;
+  const bool use_diag = kExtras && group == 0 && (p.flags & AGG_DIAG) && (p.kept_bits != nullptr || n_drop > 0);
   const uint32_t* kbits = p.kept_bits ? p.kept_bits + (int64_t)b * ((g.NQ + 31) / 32) : nullptr;
   const int64_t q_wave = q_begin + wave * kWaveQ;
   // first element of query (qb, j, c)'s row of this head in Q, K, V and O
@@ -826,8 +846,34 @@ __device__ __forceinline__ bool attend(const AttnArgs& p, int b, int h, int64_t 
     }
   };
 
-  const bool done = key_loop<kSrc, kGen, kQB, kJ>(w, lds, src, ntiles, last_valid, tid, wave, fa, G,
-                                                  first_tile);
+  const bool done = key_loop<kSrc, kGen, kSplit, kQB, kJ>(w, lds, src, ntiles, last_valid, tid, wave,
+                                                          fa, G, first_tile);
+  if (kSplit) {
+    // a loop passes one barrier per tile: the shorter one makes up for its missing tile
+    if (ntiles < half) lds_barrier();
+    __syncthreads();  // both groups are done with their tiles
+    // [register][wavefront][lane], over the second group's tiles
+    f32x4* over = reinterpret_cast<f32x4*>(tiles + kTileLds) + tid;
+    float* over_l = reinterpret_cast<float*>(tiles + kTileLds) + kQB * kJ * 4 * 4 * kAttnThreads + tid;
+    static_assert(!kSplit || kQB * kJ * (4 * 16 + 4) * kAttnThreads <= kTileLds * 2, "fits the group's LDS");
+    if (group) {
+#pragma unroll
+      for (int i = 0; i < kQB * kJ; ++i) {
+#pragma unroll
+        for (int dt = 0; dt < 4; ++dt) over[(4 * i + dt) * kAttnThreads] = w.O[i / kJ][i % kJ][dt];
+        over_l[i * kAttnThreads] = w.L[i / kJ][i % kJ][0];
+      }
+    }
+    __syncthreads();
+    if (!group) {
+#pragma unroll
+      for (int i = 0; i < kQB * kJ; ++i) {
+#pragma unroll
+        for (int dt = 0; dt < 4; ++dt) w.O[i / kJ][i % kJ][dt] += over[(4 * i + dt) * kAttnThreads];
+        w.L[i / kJ][i % kJ][0] += over_l[i * kAttnThreads];
+      }
+    }
+  }
   float l_fin[kQB][kJ];
   bool unsafe = false;
 #pragma unroll
@@ -836,7 +882,7 @@ __device__ __forceinline__ bool attend(const AttnArgs& p, int b, int h, int64_t 
     for (int j = 0; j < kJ; ++j) {
       l_fin[qb][j] = kGen ? quad_sum(w.la[qb][j]) : w.L[qb][j][0];
       // a sum outside [2^-90, 2^90] (or NaN): the unreferenced exponentials were not safe
-      unsafe = unsafe || !(l_fin[qb][j] < kSumHi) || !(l_fin[qb][j] > kSumLo);
+      unsafe = unsafe || (group == 0 && (!(l_fin[qb][j] < kSumHi) || !(l_fin[qb][j] > kSumLo)));
     }
   if (!kGen) {
     if (!done) return false;  // uniform: decided by a workgroup-wide vote inside the loop
@@ -849,6 +895,7 @@ __device__ __forceinline__ bool attend(const AttnArgs& p, int b, int h, int64_t 
   // Each wavefront instead turns its tile, a query block at a time, through a private part of the
   // (now idle) K/V LDS and writes whole 128-byte (query, head) rows, eight per instruction.
   __syncthreads();  // every wavefront is done with the K/V tiles
+  if (group) return true;
   uint16_t* epi = smem + wave * (16 * kJ * kEpiStride);
 #pragma unroll
   for (int qb = 0; qb < kQB; ++qb) {
@@ -968,16 +1015,27 @@ __device__ __forceinline__ uint64_t* redo_slot(const AttnArgs& p, const Work& w)
 // kTailQ: queries of the launch's narrow workgroups (0: it has none).
 template <int kSrc, int kTailQ>
 __global__ __launch_bounds__(kAttnThreads, kBlocksPerCu) void sga_attn_kernel(AttnArgs p) {
+  __shared__ __align__(16) uint16_t tiles[kTileLds];
   Work w;
   if (!workgroup_work(p, w)) return;
   bool done;
   if (kTailQ != 0 && w.tail) {
     constexpr int kTailQB = kTailQ == 192 ? 3 : 2;  // blocks of one 16-query tile
-    done = attend<kSrc, false, kTailQB, 1>(p, w.b, w.h, w.q_begin, w.q_end);
+    done = attend<kSrc, false, kTailQB, 1>(p, tiles, w.b, w.h, w.q_begin, w.q_end);
   } else {
-    done = attend<kSrc, false, 2, 2>(p, w.b, w.h, w.q_begin, w.q_end);
+    done = attend<kSrc, false, 2, 2>(p, tiles, w.b, w.h, w.q_begin, w.q_end);
   }
   if (!done && threadIdx.x == 0) *redo_slot(p, w) = kRedoMark;
+}
+
+// A launch of few workgroups: 128 queries each, eight wavefronts.
+template <int kSrc>
+__global__ __launch_bounds__(2 * kAttnThreads, 2) void sga_attn_split_kernel(AttnArgs p) {
+  __shared__ __align__(16) uint16_t tiles[2 * kTileLds];
+  Work w;
+  if (!workgroup_work(p, w)) return;
+  if (!attend<kSrc, false, 2, 1, true>(p, tiles, w.b, w.h, w.q_begin, w.q_end) && threadIdx.x == 0)
+    *redo_slot(p, w) = kRedoMark;
 }
 
 // The general path is a kernel of its own, launched behind the first on the same stream: it is
@@ -986,11 +1044,12 @@ __global__ __launch_bounds__(kAttnThreads, kBlocksPerCu) void sga_attn_kernel(At
 // are redone at full width with the queries beyond their own left out.
 template <int kSrc>
 __global__ __launch_bounds__(kAttnThreads, kBlocksPerCu) void sga_attn_general_kernel(AttnArgs p) {
+  __shared__ __align__(16) uint16_t tiles[kTileLds];
   Work w;
   if (!workgroup_work(p, w)) return;
   if (*redo_slot(p, w) != kRedoMark) return;  // same value in every lane
   __syncthreads();  // every wavefront has read the mark before any of them overwrites it
-  attend<kSrc, true, 2, 2>(p, w.b, w.h, w.q_begin, w.q_end);
+  attend<kSrc, true, 2, 2>(p, tiles, w.b, w.h, w.q_begin, w.q_end);
 }
 
 // Launch plan: which workgroups a pair's queries are cut into.
@@ -1037,7 +1096,13 @@ static double launch_time(int64_t full, int64_t tail, const TileCost& c) {
 
 static TilePlan plan_tiles(int64_t NQ, int npairs, int64_t key_tiles) {
   const int64_t most = NQ / kQTile;
-  TilePlan best = {(int)((NQ + kQTile - 1) / kQTile), 0, 0, 0};
+  TilePlan best = {(int)((NQ + kQTile - 1) / kQTile), 0, 0, 0, 0};
+  // At most one narrow workgroup per CU: eight wavefronts that share the keys give each SIMD two to
+  // alternate between.  The call, us, four / eight wavefronts: 2 frames of 37x37 with 8 heads, every
+  // token a key (43 key tiles), 30.2 / 25.0; through the index list 42.3 / 35.2; one frame of 37x37
+  // with 16 heads (22 tiles) 18.7 / 17.6.  Under four key tiles there is nothing to share.
+  if (key_tiles >= 4 && npairs <= kCus && npairs * ((NQ + 127) / 128) <= kCus)
+    return {0, (int)((NQ + 127) / 128), 128, 1, 1};
   if (npairs * NQ > INT32_MAX) return best;  // far past the sizes at which a tail matters
   // With at least a pair per CU the rounds are many, and what is left to gain are the queries
   // that do not exist; the tails then follow their pair's other tiles, whose keys they share.
@@ -1058,7 +1123,7 @@ static TilePlan plan_tiles(int64_t NQ, int npairs, int64_t key_tiles) {
       const double t = by_pair ? n + m * c.paired : launch_time(npairs * n, npairs * m, c);
       if (t < least) {
         least = t;
-        best = {(int)n, (int)m, c.queries, by_pair ? 0 : 1};
+        best = {(int)n, (int)m, c.queries, by_pair ? 0 : 1, 0};
       }
     }
   }
@@ -1070,7 +1135,8 @@ static void launch_source(const AttnArgs& p, hipStream_t st) {
   const dim3 grid((unsigned)(first_list(p.plan, p.npairs).groups + second_list(p.plan, p.npairs).groups));
   const dim3 block(kAttnThreads);
   const int tail_q = p.plan.n_tail ? p.plan.tail_q : 0;
-  if (tail_q == 0) hipLaunchKernelGGL((sga_attn_kernel<kSrc, 0>), grid, block, 0, st, p);
+  if (p.plan.split) hipLaunchKernelGGL(sga_attn_split_kernel<kSrc>, grid, dim3(2 * kAttnThreads), 0, st, p);
+  else if (tail_q == 0) hipLaunchKernelGGL((sga_attn_kernel<kSrc, 0>), grid, block, 0, st, p);
   else if (tail_q == 192) hipLaunchKernelGGL((sga_attn_kernel<kSrc, 192>), grid, block, 0, st, p);
   else hipLaunchKernelGGL((sga_attn_kernel<kSrc, 128>), grid, block, 0, st, p);
   hipLaunchKernelGGL(sga_attn_general_kernel<kSrc>, grid, block, 0, st, p);
