@@ -57,6 +57,7 @@ def make_shape(B, N, n_h, n_w, n_special, H, D, s_h, s_w, keep_first_frame=1,
 
 
 _lib = None
+_raw_stream = None
 
 EXPORTS = [
     "agg_status_string", "agg_sigma_to_strides", "agg_kv_count", "agg_kv_indices_host",
@@ -148,6 +149,9 @@ def lib():
     L.agg_static_scratch_bytes.restype = ctypes.c_size_t
     L.agg_static_scratch_bytes.argtypes = []
     L.agg_kv_subsample_static.argtypes = [shp, vp, vp, vp, vp, vp, vp, vp, vp]
+    global _raw_stream
+    # the current stream's handle without building a Stream object for it (3 us a call)
+    _raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
     _lib = L
     return L
 
@@ -158,22 +162,25 @@ def _check(status: int, where: str):
 
 
 def _ptr(t):
-    """Device (or host) address of a torch tensor / numpy array / raw int / None."""
-    if t is None:
-        return None
-    if isinstance(t, int):
-        return ctypes.c_void_p(t)
+    """Device (or host) address of a torch tensor / numpy array / raw int / None, as the plain
+    number that the declared argument types take (a ctypes object per argument cost as much as the
+    call itself)."""
+    if t is None or isinstance(t, int):
+        return t
     if hasattr(t, "data_ptr"):
-        return ctypes.c_void_p(t.data_ptr())
-    return ctypes.c_void_p(t.ctypes.data)
+        return t.data_ptr()
+    return t.ctypes.data
 
 
 def _stream(stream):
-    if stream is None:
-        import torch
+    """Handle of `stream`, by default of the current device's current stream."""
+    if stream is not None:
+        return int(stream)
+    import torch
 
-        stream = torch.cuda.current_stream().cuda_stream
-    return ctypes.c_void_p(int(stream))
+    if _raw_stream is not None and torch.cuda.is_initialized():
+        return _raw_stream(torch.cuda.current_device())
+    return torch.cuda.current_stream().cuda_stream
 
 
 def status_string(status: int) -> str:
