@@ -664,16 +664,23 @@ constexpr int kTileLds = 2 * kLdsTiles * kTileElems;  // elements: K tiles, then
 // two paths.  Returns false, without storing anything, when the fast path met a row it cannot
 // handle.
 // tiles: kTileLds elements of LDS per four wavefronts.
-// kSplit (fast path): eight wavefronts; the first four take the extras and the first half of the
-// key tiles, the others the second half.  Without a reference the two halves' sums and accumulators
-// just add: the second group's go through LDS to the first, which finishes the rows.
-template <int kSrc, bool kGen, int kQB, int kJ, bool kSplit = false>
+// kMode:
+//   kAlone      four wavefronts.
+//   kSplitKeys  (fast path) eight: the first four take the extras and the first half of the key
+//               tiles, the others the second half.  Without a reference the two halves' sums and
+//               accumulators just add: the second group's go through LDS to the first, which
+//               finishes the rows.
+//   kTwin       eight: both groups do the same (so that their barriers match), the first stores.
+enum { kAlone, kSplitKeys, kTwin };
+template <int kSrc, bool kGen, int kQB, int kJ, int kMode = kAlone>
 __device__ __forceinline__ bool attend(const AttnArgs& p, uint16_t* tiles, int b, int h,
                                        int64_t q_begin, int64_t q_end) {
+  constexpr bool kSplit = kMode == kSplitKeys;
   static_assert(!(kGen && kSplit), "the general path's halves would need a common reference");
   constexpr int kWaveQ = wave_queries(kQB, kJ);
   const Geom& g = p.g;
-  const int group = kSplit ? __builtin_amdgcn_readfirstlane((int)threadIdx.x / kAttnThreads) : 0;
+  const int group =
+      kMode != kAlone ? __builtin_amdgcn_readfirstlane((int)threadIdx.x / kAttnThreads) : 0;
   uint16_t* smem = tiles + group * kTileLds;
   u32x4* lds = reinterpret_cast<u32x4*>(smem);
   const int tid = threadIdx.x - group * kAttnThreads;
@@ -686,8 +693,8 @@ __device__ __forceinline__ bool attend(const AttnArgs& p, uint16_t* tiles, int b
   // this group's key tiles: first_tile_no .. first_tile_no + ntiles - 1
   const int all_tiles = (int)(g.M_pad / kTileRows);
   const int half = kSplit ? (all_tiles + 1) / 2 : all_tiles;
-  const int skip = group ? half : 0;
-  const int ntiles = group ? all_tiles - half : half;
+  const int skip = kSplit && group ? half : 0;
+  const int ntiles = kSplit && group ? all_tiles - half : half;
   const int64_t rows_here = min(g.M - (int64_t)skip * kTileRows, (int64_t)ntiles * kTileRows);
   const int last_valid = (int)(rows_here - (int64_t)(ntiles - 1) * kTileRows);  // 1..64
   KvSource src;
@@ -717,8 +724,9 @@ __device__ __forceinline__ bool attend(const AttnArgs& p, uint16_t* tiles, int b
   // ordinary and per-frame attention have no extras; where that is known at compile time the fast
   // path's code is a third shorter (the general path's would spill)
   constexpr bool kExtras = kSrc != kSrcRows || kGen;
-  const bool use_mean = kExtras && group == 0 && (p.flags & AGG_MEAN) && n_drop > 0;
-  const bool use_diag = kExtras && group == 0 && (p.flags & AGG_DIAG) && (p.kept_bits != nullptr || n_drop > 0);
+  const bool takes = kExtras && !(kSplit && group);
+  const bool use_mean = takes && (p.flags & AGG_MEAN) && n_drop > 0;
+  const bool use_diag = takes && (p.flags & AGG_DIAG) && (p.kept_bits != nullptr || n_drop > 0);
   const uint32_t* kbits = p.kept_bits ? p.kept_bits + (int64_t)b * ((g.NQ + 31) / 32) : nullptr;
   const int64_t q_wave = q_begin + wave * kWaveQ;
   // first element of query (qb, j, c)'s row of this head in Q, K, V and O
@@ -1028,14 +1036,17 @@ __global__ __launch_bounds__(kAttnThreads, kBlocksPerCu) void sga_attn_kernel(At
   if (!done && threadIdx.x == 0) *redo_slot(p, w) = kRedoMark;
 }
 
-// A launch of few workgroups: 128 queries each, eight wavefronts.
+// A launch of few workgroups: 128 queries each, eight wavefronts.  Rows that leave the fast path's
+// range are redone here by the general path, which at this width needs no more registers: an idle
+// second launch would be a fifth of a small call's time.
 template <int kSrc>
 __global__ __launch_bounds__(2 * kAttnThreads, 2) void sga_attn_split_kernel(AttnArgs p) {
   __shared__ __align__(16) uint16_t tiles[2 * kTileLds];
   Work w;
   if (!workgroup_work(p, w)) return;
-  if (!attend<kSrc, false, 2, 1, true>(p, tiles, w.b, w.h, w.q_begin, w.q_end) && threadIdx.x == 0)
-    *redo_slot(p, w) = kRedoMark;
+  if (attend<kSrc, false, 2, 1, kSplitKeys>(p, tiles, w.b, w.h, w.q_begin, w.q_end)) return;
+  __syncthreads();
+  attend<kSrc, true, 2, 1, kTwin>(p, tiles, w.b, w.h, w.q_begin, w.q_end);
 }
 
 // The general path is a kernel of its own, launched behind the first on the same stream: it is
@@ -1100,8 +1111,8 @@ static TilePlan plan_tiles(int64_t NQ, int npairs, int64_t key_tiles) {
   // At most one narrow workgroup per CU: eight wavefronts that share the keys give each SIMD two to
   // alternate between.  The call, us, four / eight wavefronts: 2 frames of 37x37 with 8 heads, every
   // token a key (43 key tiles), 30.2 / 25.0; through the index list 42.3 / 35.2; one frame of 37x37
-  // with 16 heads (22 tiles) 18.7 / 17.6.  Under four key tiles there is nothing to share.
-  if (key_tiles >= 4 && npairs <= kCus && npairs * ((NQ + 127) / 128) <= kCus)
+  // with 16 heads (22 tiles) 18.7 / 17.6.  One key tile cannot be shared.
+  if (key_tiles >= 2 && npairs <= kCus && npairs * ((NQ + 127) / 128) <= kCus)
     return {0, (int)((NQ + 127) / 128), 128, 1, 1};
   if (npairs * NQ > INT32_MAX) return best;  // far past the sizes at which a tail matters
   // With at least a pair per CU the rounds are many, and what is left to gain are the queries
@@ -1135,8 +1146,11 @@ static void launch_source(const AttnArgs& p, hipStream_t st) {
   const dim3 grid((unsigned)(first_list(p.plan, p.npairs).groups + second_list(p.plan, p.npairs).groups));
   const dim3 block(kAttnThreads);
   const int tail_q = p.plan.n_tail ? p.plan.tail_q : 0;
-  if (p.plan.split) hipLaunchKernelGGL(sga_attn_split_kernel<kSrc>, grid, dim3(2 * kAttnThreads), 0, st, p);
-  else if (tail_q == 0) hipLaunchKernelGGL((sga_attn_kernel<kSrc, 0>), grid, block, 0, st, p);
+  if (p.plan.split) {
+    hipLaunchKernelGGL(sga_attn_split_kernel<kSrc>, grid, dim3(2 * kAttnThreads), 0, st, p);
+    return;
+  }
+  if (tail_q == 0) hipLaunchKernelGGL((sga_attn_kernel<kSrc, 0>), grid, block, 0, st, p);
   else if (tail_q == 192) hipLaunchKernelGGL((sga_attn_kernel<kSrc, 192>), grid, block, 0, st, p);
   else hipLaunchKernelGGL((sga_attn_kernel<kSrc, 128>), grid, block, 0, st, p);
   hipLaunchKernelGGL(sga_attn_general_kernel<kSrc>, grid, block, 0, st, p);

@@ -130,11 +130,11 @@ def test_mean_split_by_heads(H, B, nq):
 
 
 @pytest.mark.parametrize("extreme", [False, True])
-@pytest.mark.parametrize("nq,s_w", [(250, 1), (257, 1), (3073, 1), (3200, 1), (4160, 3)])
+@pytest.mark.parametrize("nq,s_w", [(66, 1), (130, 1), (250, 1), (257, 1), (3073, 1), (3200, 1), (4160, 3)])
 def test_keys_shared_by_two_groups(nq, s_w, extreme):
     """At most one workgroup per CU: two groups of wavefronts share the key tiles, an even and an odd
-    number of them, 4 (the fewest that are shared), 5, 49, 50 and 22.  `extreme`: rows that leave the
-    fast path's range, as in test_narrow_tail_workgroups."""
+    number of them: 2 (the fewest that are shared), 3, 4, 5, 49, 50 and 22.  `extreme`: rows that leave
+    the fast path's range, as in test_narrow_tail_workgroups; the same launch redoes them."""
     shape = agg.make_shape(1, 1, 1, nq, 0, 2, 64, 1, s_w, 0)
     q, k, v = inputs.iid_qkv(1, nq, 2, 64, seed=6900 + nq, device="cuda")
     if extreme:
