@@ -42,8 +42,8 @@
 //     invariant to the reference, float/bf16 exponents cover 2^+-126, and the
 //     per-score work shrinks to exp + convert.  A row whose sum leaves
 //     [2^-90, 2^90] (logits beyond about +-60 nats) makes the whole workgroup
-//     redo its rows in the general path (a second kernel behind this one, see
-//     the end of the file); ordinary attention logits never get there.  The
+//     redo its rows in the general path (in place, or by a second kernel behind this
+//     one, see launch_source); ordinary attention logits never get there.  The
 //     sums are checked every few tiles, so an overflow ends the fast pass early.
 //   * General path: the same pipeline with a per-row reference.  The score MFMAs start from
 //     an accumulator holding minus the reference instead of zero, so the scores come out
@@ -1021,7 +1021,9 @@ __device__ __forceinline__ uint64_t* redo_slot(const AttnArgs& p, const Work& w)
 }
 
 // kTailQ: queries of the launch's narrow workgroups (0: it has none).
-template <int kSrc, int kTailQ>
+// kRedo: a workgroup redoes its own rows by the general path, 128 queries at a time (at that width
+// it needs no more registers than the fast path), instead of leaving the mark for a second launch.
+template <int kSrc, int kTailQ, bool kRedo>
 __global__ __launch_bounds__(kAttnThreads, kBlocksPerCu) void sga_attn_kernel(AttnArgs p) {
   __shared__ __align__(16) uint16_t tiles[kTileLds];
   Work w;
@@ -1033,7 +1035,16 @@ __global__ __launch_bounds__(kAttnThreads, kBlocksPerCu) void sga_attn_kernel(At
   } else {
     done = attend<kSrc, false, 2, 2>(p, tiles, w.b, w.h, w.q_begin, w.q_end);
   }
-  if (!done && threadIdx.x == 0) *redo_slot(p, w) = kRedoMark;
+  if (done) return;
+  if (!kRedo) {
+    if (threadIdx.x == 0) *redo_slot(p, w) = kRedoMark;
+    return;
+  }
+#pragma unroll 1
+  for (int64_t q = w.q_begin; q < w.q_end; q += kWaves * wave_queries(2, 1)) {
+    __syncthreads();  // the LDS is free
+    attend<kSrc, true, 2, 1>(p, tiles, w.b, w.h, q, min(w.q_end, q + kWaves * wave_queries(2, 1)));
+  }
 }
 
 // A launch of few workgroups: 128 queries each, eight wavefronts.  Rows that leave the fast path's
@@ -1141,19 +1152,32 @@ static TilePlan plan_tiles(int64_t NQ, int npairs, int64_t key_tiles) {
   return best;
 }
 
+template <int kSrc, bool kRedo>
+static void launch_fast(const AttnArgs& p, dim3 grid, hipStream_t st) {
+  const dim3 block(kAttnThreads);
+  const int tail_q = p.plan.n_tail ? p.plan.tail_q : 0;
+  if (tail_q == 0) hipLaunchKernelGGL((sga_attn_kernel<kSrc, 0, kRedo>), grid, block, 0, st, p);
+  else if (tail_q == 192) hipLaunchKernelGGL((sga_attn_kernel<kSrc, 192, kRedo>), grid, block, 0, st, p);
+  else hipLaunchKernelGGL((sga_attn_kernel<kSrc, 128, kRedo>), grid, block, 0, st, p);
+}
+
 template <int kSrc>
 static void launch_source(const AttnArgs& p, hipStream_t st) {
   const dim3 grid((unsigned)(first_list(p.plan, p.npairs).groups + second_list(p.plan, p.npairs).groups));
-  const dim3 block(kAttnThreads);
-  const int tail_q = p.plan.n_tail ? p.plan.tail_q : 0;
   if (p.plan.split) {
     hipLaunchKernelGGL(sga_attn_split_kernel<kSrc>, grid, dim3(2 * kAttnThreads), 0, st, p);
-    return;
+  } else if (p.g.M_pad / kTileRows >= 8 && p.g.M_pad / kTileRows < 128) {
+    // An idle second launch is 1 to 2 % of a call with few key tiles (us with it / without: per-frame,
+    // 90 frames of 37x37, 22 tiles, 707 / 698; 3 frames subsampled, 16 tiles, 43.8 / 42.0; 10 frames,
+    // 122 tiles, 385 / 383), and where one query needs the general path the others no longer wait for
+    // it (10 frames, attention alone: 624 / 373; were every workgroup to need it, 608 / 655).  Under
+    // eight tiles the larger kernel costs more (47 / 53 at 5 tiles), and with long key loops the
+    // idle launch is lost in them.
+    launch_fast<kSrc, true>(p, grid, st);
+  } else {
+    launch_fast<kSrc, false>(p, grid, st);
+    hipLaunchKernelGGL(sga_attn_general_kernel<kSrc>, grid, dim3(kAttnThreads), 0, st, p);
   }
-  if (tail_q == 0) hipLaunchKernelGGL((sga_attn_kernel<kSrc, 0>), grid, block, 0, st, p);
-  else if (tail_q == 192) hipLaunchKernelGGL((sga_attn_kernel<kSrc, 192>), grid, block, 0, st, p);
-  else hipLaunchKernelGGL((sga_attn_kernel<kSrc, 128>), grid, block, 0, st, p);
-  hipLaunchKernelGGL(sga_attn_general_kernel<kSrc>, grid, block, 0, st, p);
 }
 
 hipError_t launch_attn(const Geom& g, uint32_t flags, float scale, float mean_bias, const void* Q,

@@ -24,7 +24,7 @@ def test_pairs_around_the_xcd_count(B, H, nq):
     _idx_case(shape, q, k, v, "pairs %d" % (B * H))
 
 
-# (B, queries, H, column stride): the strides leave 70 to 150 keys, so that every row can be checked
+# (B, queries, H, column stride): the strides leave 70 to 520 keys, so that every row can be checked
 TAILS = [
     (1, 1000, 16, 9),      # narrow workgroups only (128 queries)
     (1, 9192, 16, 97),     # whole rounds of full-width workgroups, then 128-query ones
@@ -32,6 +32,10 @@ TAILS = [
     (1, 24984, 12, 301),   # ... over pairs that share the XCDs
     (1, 8193, 16, 97),     # one query beyond whole rounds
     (2, 2049, 8, 31),      # two batch elements
+    # eight key tiles and more: rows that leave the fast path's range are redone by the same launch
+    (1, 2600, 16, 5),
+    (1, 4096, 16, 8),      # full-width workgroups only
+    (1, 13740, 16, 27),
 ]
 
 
