@@ -336,6 +336,7 @@ struct TileCopier {
   // to the eight lanes that fetch it, a tile ahead of their use.  (Every lane reading and scaling
   // its own two ids cost 17 vector instructions a tile instead of 8, in a loop that the vector ALU
   // bounds: 40 frames 2768 us against 2658, 100 frames 32.4 ms against 31.7, 8 frames 158 against 143.)
+  uint32_t lane;           // of the wavefront
   uint32_t list_at;        // byte offset of this lane's id for the tile after the next
   uint32_t id;             // its id for the tile after the next to be copied
   uint32_t from[2];        // next tile to be copied: byte offset of the rows this lane fetches
@@ -369,10 +370,11 @@ struct TileCopier {
       }
     }
     if (kSrc == kSrcIndexed) {
-      const uint32_t l = tid & 15;
+      lane = tid & 63;
+      const uint32_t l = lane & 15;
       list_at = ((l & 8) * 4u + wave * 8u + (l & 7)) * 4u;
       fetch_ids();
-      spread_ids(tid & 63);
+      spread_ids();
       fetch_ids();
     }
   }
@@ -381,7 +383,7 @@ struct TileCopier {
     id = *reinterpret_cast<const uint32_t*>(reinterpret_cast<const char*>(src.list) + at);
     list_at += kTileRows * 4u;
   }
-  __device__ __forceinline__ void spread_ids(uint32_t lane) {
+  __device__ __forceinline__ void spread_ids() {
     // an id outside the sequence cannot leave it
     const int base = (int)__umul24(min(id, src.max_token), src.row_bytes);
 #pragma unroll
@@ -426,7 +428,7 @@ struct TileCopier {
         dma16(src.k, from[hh] + vk[hh], mk + hh * kAttnThreads * 16);
         dma16(src.v, from[hh] + vv[hh], mv + hh * kAttnThreads * 16);
       }
-      spread_ids(threadIdx.x & 63);  // the next tile's offsets; its ids came with the last wait
+      spread_ids();  // the next tile's offsets; its ids came with the last wait
       fetch_ids();                   // and the ids after those
     }
     ++tnext;
@@ -694,11 +696,15 @@ __device__ __forceinline__ bool attend(const AttnArgs& p, uint16_t* tiles, int b
   static_assert(!(kGen && kSplit), "the general path's halves would need a common reference");
   constexpr int kWaveQ = wave_queries(kQB, kJ);
   const Geom& g = p.g;
-  const int group =
-      kMode != kAlone ? __builtin_amdgcn_readfirstlane((int)threadIdx.x / kAttnThreads) : 0;
+  // The general path starts from an opaque thread number, so that the addresses it has in common
+  // with a fast pass ahead of it in the same kernel are worked out again: held across the fast
+  // key loop they spilled (up to 33 registers).
+  int thread = threadIdx.x;
+  if (kGen) asm volatile("" : "+v"(thread));
+  const int group = kMode != kAlone ? __builtin_amdgcn_readfirstlane(thread / kAttnThreads) : 0;
   uint16_t* smem = tiles + group * kTileLds;
   u32x4* lds = reinterpret_cast<u32x4*>(smem);
-  const int tid = threadIdx.x - group * kAttnThreads;
+  const int tid = thread - group * kAttnThreads;
   const int lane = tid & 63;
   const int wave = tid >> 6;
   const int c = lane & 15;
@@ -737,7 +743,8 @@ __device__ __forceinline__ bool attend(const AttnArgs& p, uint16_t* tiles, int b
   // caller's list: membership comes from a bitmap, the dropped count from device memory
   const int64_t n_drop = p.nd_dev ? (int64_t)p.nd_dev[b] : g.n_dropped;
   // ordinary and per-frame attention have no extras; where that is known at compile time the fast
-  // path's code is a third shorter (the general path's would spill)
+  // path's code is a third shorter (the general path's would spill: 353 registers instead of 15 in
+  // the second launch, 149 to 192 instead of none where rows are redone in place)
   constexpr bool kExtras = kSrc != kSrcRows || kGen;
   const bool takes = kExtras && !(kSplit && group);
   const bool use_mean = takes && (p.flags & AGG_MEAN) && n_drop > 0;
@@ -1036,8 +1043,14 @@ __device__ __forceinline__ uint64_t* redo_slot(const AttnArgs& p, const Work& w)
 }
 
 // kTailQ: queries of the launch's narrow workgroups (0: it has none).
-// kRedo: a workgroup redoes its own rows by the general path, 128 queries at a time (at that width
-// it needs no more registers than the fast path), instead of leaving the mark for a second launch.
+// kRedo: a workgroup redoes its own rows by the general path, 128 queries at a time, instead of
+// leaving the mark for a second launch.  At that width the general path needs no more registers
+// than the fast one, provided that nothing is held for it meanwhile: it starts from an opaque
+// thread number (attend) and reads the kernel's arguments again (they are the kernel's only
+// parameter, at the start of its argument memory).  So no instance spills, which a build test
+// checks, and each uses within 13 registers what it uses without kRedo.  Sharing both with the
+// fast path spilled 14 registers (compacted), 32 (rows) and 33 (indexed) at full width, some of
+// them in every workgroup's epilogue.
 template <int kSrc, int kTailQ, bool kRedo>
 __global__ __launch_bounds__(kAttnThreads, kBlocksPerCu) void sga_attn_kernel(AttnArgs p) {
   __shared__ __align__(16) uint16_t tiles[kTileLds];
@@ -1055,10 +1068,14 @@ __global__ __launch_bounds__(kAttnThreads, kBlocksPerCu) void sga_attn_kernel(At
     if (threadIdx.x == 0) *redo_slot(p, w) = kRedoMark;
     return;
   }
+  typedef const __attribute__((address_space(4))) AttnArgs* KernelArgs;
+  KernelArgs args = (KernelArgs)__builtin_amdgcn_kernarg_segment_ptr();
+  asm volatile("" : "+s"(args));
+  const AttnArgs& again = *(const AttnArgs*)args;
 #pragma unroll 1
   for (int64_t q = w.q_begin; q < w.q_end; q += kWaves * wave_queries(2, 1)) {
     __syncthreads();  // the LDS is free
-    attend<kSrc, true, 2, 1>(p, tiles, w.b, w.h, q, min(w.q_end, q + kWaves * wave_queries(2, 1)));
+    attend<kSrc, true, 2, 1>(again, tiles, w.b, w.h, q, min(w.q_end, q + kWaves * wave_queries(2, 1)));
   }
 }
 
@@ -1182,12 +1199,21 @@ static void launch_source(const AttnArgs& p, hipStream_t st) {
   if (p.plan.split) {
     hipLaunchKernelGGL(sga_attn_split_kernel<kSrc>, grid, dim3(2 * kAttnThreads), 0, st, p);
   } else if (p.g.M_pad / kTileRows >= 8 && p.g.M_pad / kTileRows < 128) {
-    // An idle second launch is 1 to 2 % of a call with few key tiles (us with it / without: per-frame,
-    // 90 frames of 37x37, 22 tiles, 707 / 698; 3 frames subsampled, 16 tiles, 43.8 / 42.0; 10 frames,
-    // 122 tiles, 385 / 383), and where one query needs the general path the others no longer wait for
-    // it (10 frames, attention alone: 624 / 373; were every workgroup to need it, 608 / 655).  Under
-    // eight tiles the larger kernel costs more (47 / 53 at 5 tiles), and with long key loops the
-    // idle launch is lost in them.
+    // An idle second launch is 1 to 4 % of a call with few key tiles, and where one query needs the
+    // general path the others no longer wait for it.  Under eight tiles the larger kernel costs more
+    // (50 frames of 16x16, 5 tiles: 47 / 53 us), and with long key loops the idle launch is lost in
+    // them.  Attention alone, us, second launch / redo in place, by the width of the last workgroups:
+    //   full  compacted, 12 frames of 16x16, 16 tiles          26.5 / 24.8
+    //         compacted, 3 frames of 37x37, 12 heads, 44 tiles 50.9 / 48.9;  5 frames, 66 tiles 114.3 / 112.2
+    //         compacted, 30 frames, 12 heads, 101 tiles         661 / 658
+    //         indexed, 12 frames of 16x16, 16 tiles            27.5 / 26.0;  5 frames, 45 tiles 87.8 / 86.0
+    //         rows, per-frame, 5 frames, 22 tiles 44.1 / 42.1;  5 frames, 108 tiles 172.8 / 170.5
+    //   192   compacted, 2 frames, 33 tiles 33.5 / 32.0;  10 frames, 122 tiles 330.7 / 327.9
+    //         indexed, 10 frames 353.9 / 351.0;  rows, 2 frames, 43 tiles 38.2 / 36.7
+    //   128   compacted, 3 frames, 44 tiles 55.4 / 53.9;  rows, per-frame, 90 frames, 22 tiles 689 / 665
+    // One query out of range / every workgroup: compacted, 10 frames 576 / 355 and 571 / 607 (the one
+    // loss: 128 queries at a time read the keys twice); rows, 5 frames, 108 tiles 378 / 233 and
+    // 285 / 291; per-frame, 90 frames 738 / 683 and 1894 / 1580.
     launch_fast<kSrc, true>(p, grid, st);
   } else {
     launch_fast<kSrc, false>(p, grid, st);

@@ -304,3 +304,28 @@ def test_projection_kernels_leave_m0_to_their_copy_statements(tmp_path):
     assert seen_copy >= 16, "the copy statements were not found"
     assert not offenders, offenders[:5]
     assert "scratch_load" not in text and "scratch_store" not in text
+
+
+def test_attention_kernels_that_redo_rows_do_not_spill(tmp_path):
+    """The attention kernels that redo rows themselves hold two paths' code; nothing of the second may
+    lie in scratch memory while the first runs, or every workgroup pays for it.  (The kernel of the
+    second launch, which only ever runs the general path at full width, does spill.)"""
+    import subprocess
+
+    from paper_2512_02541_amd import build as b
+
+    out = tmp_path / "agg_attn.s"
+    cmd = [b.HIPCC, *b.FLAGS, "-I", os.path.join(ROOT, "include"), "-I", b.CSRC, "-S",
+           "--cuda-device-only", os.path.join(b.CSRC, "agg_attn.hip"), "-o", str(out)]
+    subprocess.check_call(cmd, stderr=subprocess.DEVNULL)
+    seen, spilled = 0, []
+    for kernel in re.split(r"^  - \.", out.read_text(), flags=re.M):
+        name = re.search(r"\.name: +\S*(sga_attn_(?:split_)?kernel\S*)", kernel)
+        if name:
+            seen += 1
+            field = {f: int(re.search(r"\.%s: +(\d+)" % f, kernel).group(1))
+                     for f in ("vgpr_spill_count", "private_segment_fixed_size")}
+            if any(field.values()):
+                spilled.append((name.group(1), field))
+    assert seen == 21, "three sources, three widths with and without the redo, and the split kernels"
+    assert not spilled, spilled
