@@ -375,10 +375,12 @@ def test_idx_path_full_size():
 
 # ----------------------------------------------------------------------------
 # Key counts around the tile edges: the key loop walks 64-key tiles through three LDS buffers
-# (unrolled by three), masks the tail of the last tile only, and checks its row sums every 24
-# tiles.  One frame with strides (1,1) makes every token a key, so M = NQ can be set at will:
-# 1..8 tiles and two counts beyond the first sum check, each with a full, a one-key and a
-# 63-key last tile, through all three ways the kernel fetches its tiles.
+# (unrolled by three) and masks the tail of the last tile only.  One frame with strides (1,1) makes
+# every token a key, so M = NQ can be set at will: 1..8 and 24..26 tiles, each with a full, a one-key
+# and a 63-key last tile, through all three ways the kernel fetches its tiles.  From two tiles on
+# these calls are small enough for the kernel whose two groups of wavefronts share the key tiles;
+# the same counts through the other kernels, which check their row sums every 24 tiles, are in
+# test_gpu_variants.py.
 # ----------------------------------------------------------------------------
 TILE_EDGE_COUNTS = [64 * t + r for t in (0, 1, 2, 3, 4, 5, 6, 7, 24, 25) for r in (0, 1, 63)
                     if 64 * t + r > 0]
@@ -411,9 +413,9 @@ def test_key_counts_around_tile_edges(nkeys):
 
 @pytest.mark.parametrize("nq", [1, 2, 31, 32, 33, 63, 64, 65, 255, 256, 257, 511, 512, 513, 1025])
 def test_query_counts_around_tile_edges(nq):
-    """Query counts around the 32-query block, the 64-query wavefront and the 256-query
-    workgroup tile, with a subsampled key set (one frame, pi^3 rule, strides (1,3)) and both
-    extras: whole path against the oracle, then the index-driven path against the first."""
+    """Query counts around the tile of 16, the wavefront's 32 and the workgroup's 128 queries, with a
+    subsampled key set (one frame, pi^3 rule, strides (1,3)) and both extras: whole path against the
+    oracle, then the index-driven path against the first.  (Small calls: see above.)"""
     shape = agg.make_shape(1, 1, 1, nq, 0, 3, 64, 1, 3, 0)
     q, k, v = inputs.iid_qkv(1, nq, 3, 64, seed=7000 + nq, device="cuda")
     run_case(shape, q, k, v, what="query edge %d" % nq)

@@ -7,7 +7,8 @@ import torch
 from oracle import sga_oracle as orc
 from paper_2512_02541_amd import binding as agg
 from paper_2512_02541_amd import harness, inputs
-from test_gpu_parity import _idx_case, check_output, check_subsample, oshape, run_case
+from test_gpu_parity import (TILE_EDGE_COUNTS, _idx_case, check_list_case, check_output,
+                             check_subsample, oshape, run_case)
 
 pytestmark = pytest.mark.gpu
 
@@ -26,11 +27,11 @@ def test_pairs_around_the_xcd_count(B, H, nq):
 
 # (B, queries, H, column stride): the strides leave 70 to 520 keys, so that every row can be checked
 TAILS = [
-    (1, 1000, 16, 9),      # narrow workgroups only (128 queries)
-    (1, 9192, 16, 97),     # whole rounds of full-width workgroups, then 128-query ones
-    (1, 13740, 16, 97),    # ... then 192-query ones
+    (1, 1000, 16, 9),      # at most a workgroup per CU: the keys are shared by two groups
+    (1, 9192, 16, 97),     # narrow workgroups only (192 queries)
+    (1, 13740, 16, 97),    # whole rounds of full-width workgroups, then 192-query ones
     (1, 24984, 12, 301),   # ... over pairs that share the XCDs
-    (1, 8193, 16, 97),     # one query beyond whole rounds
+    (1, 8193, 16, 97),     # narrow workgroups only (192), the last of 129 queries
     (2, 2049, 8, 31),      # two batch elements
     # eight key tiles and more: rows that leave the fast path's range are redone by the same launch
     (1, 2600, 16, 5),
@@ -59,8 +60,8 @@ def test_narrow_tail_workgroups(case, extreme):
 
 @pytest.mark.parametrize("L", [449, 600, 700, 769])
 def test_narrow_tail_per_frame(L):
-    """A pair per CU and more: each pair's narrow workgroup (128 queries at 449, 600 and 769, 192 at
-    700) follows its full-width ones.  449 keys are the fewest that take this order."""
+    """A pair per CU and more: each pair's narrow workgroup (128 queries at 600 and 769, 192 at 700)
+    follows its full-width ones.  449 keys, the fewest that may take this order, stay at full width."""
     shape = agg.make_shape(1, 16, 1, L, 0, 16, 64, 1, 1, 0, flags=0)
     q, k, v = inputs.iid_qkv(1, shape.NQ, 16, 64, seed=6600 + L, device="cuda")
     O, lse = harness.frame_forward(shape, q, k, v)
@@ -145,3 +146,133 @@ def test_keys_shared_by_two_groups(nq, s_w, extreme):
         q[:, ::211] = 32 * k[:, ::211]
     run_case(shape, q, k, v, what="shared keys %d" % nq)
     _idx_case(shape, q, k, v, "shared keys %d" % nq)
+
+
+# ---- the kernels of four wavefronts, which do nearly all the work of larger calls ---------------
+# Launches of at most one narrow workgroup per CU go to eight wavefronts that share the keys, so
+# the sweeps below stay beyond that.  tests/test_launch_plan.py checks, without a GPU, that each size
+# here is cut as it says.
+QUERIES_BY_WIDTH = {0: 4096, 192: 2748, 128: 4122}  # last workgroups' width -> queries, with 16 heads
+
+
+def _shape_of_keys(B, nq, nkeys, H):
+    """nq queries, nkeys kept rows: all but one of them special tokens."""
+    return agg.make_shape(B, 1, 1, nq - nkeys + 1, nkeys - 1, H, 64, 1, nq, 0)
+
+
+def _some_rows(nq):
+    """Both sides of every 64th row of the last two workgroups' worth, and every 61st row."""
+    end = {r + d for r in range(nq - nq % 64, max(0, nq - 600), -64) for d in (-1, 0, 1)}
+    return np.array(sorted(r for r in end | set(range(0, nq, 61)) | {nq - 2, nq - 1} if 0 <= r < nq))
+
+
+@pytest.mark.parametrize("nkeys", TILE_EDGE_COUNTS)
+def test_key_counts_of_four_wavefront_kernels(nkeys):
+    """1 to 8, 24, 25 and 26 key tiles, the last one of 1, 63 and 64 keys, at each width, compacted and
+    index-driven; and the same counts as rows in place, by per-frame attention."""
+    for width, nq in QUERIES_BY_WIDTH.items():
+        shape = _shape_of_keys(1, nq, nkeys, 16)
+        assert agg.agg_kv_count(shape)[0] == nkeys
+        q, k, v = inputs.iid_qkv(1, nq, 16, 64, seed=9100 + nkeys + width, device="cuda")
+        run_case(shape, q, k, v, rows=_some_rows(nq), what="%d keys, width %d" % (nkeys, width))
+        _idx_case(shape, q, k, v, "%d keys, width %d" % (nkeys, width))
+    _frame_case(33, nkeys, 8, 9400 + nkeys)
+
+
+def _frame_case(N, L, H, seed, spoil=None):
+    shape = agg.make_shape(1, N, 1, L, 0, H, 64, 1, 1, 0, flags=0)
+    q, k, v = inputs.iid_qkv(1, shape.NQ, H, 64, seed=seed, device="cuda")
+    if spoil:
+        q, k = spoil(q, k)
+    O, lse = harness.frame_forward(shape, q, k, v)
+    torch.cuda.synchronize()
+    rows = np.concatenate([f * L + _some_rows(L) for f in (0, N // 2, N - 1)] +
+                          [np.arange(0, shape.NQ, 211)])
+    rows = np.unique(rows)
+    want_o, want_lse = orc.frame_rows(oshape(shape), *(inputs.bf16_bits(t) for t in (q, k, v)), rows)
+    got_lse = lse.permute(1, 0, 2).reshape(1, H, shape.NQ)
+    check_output(O, got_lse, want_o, want_lse, rows, "%d frames of %d" % (N, L), q, k, shape.scale)
+
+
+# 261 pairs.  Up to six key tiles: full width throughout; with 520 keys a pair may end in a narrow
+# workgroup, by its queries beyond 1024.
+QUERY_EDGES = [1, 2, 15, 16, 17, 31, 32, 33, 63, 64, 65, 127, 128, 129, 255, 256, 257, 511, 512, 513]
+QUERY_EDGES_BY_PAIR = {1025: 128, 1087: 128, 1151: 128, 1152: 128, 1153: 192, 1215: 192, 1216: 192,
+                       1217: 0, 1280: 0}
+
+
+@pytest.mark.parametrize("nq", QUERY_EDGES + list(QUERY_EDGES_BY_PAIR))
+def test_query_counts_of_four_wavefront_kernels(nq):
+    """Query counts around the tile of 16, the wavefront of 32, 48 or 64 and the workgroup of 128, 192
+    or 256, at 9 batch elements of 29 heads."""
+    B, H = 9, 29
+    nkeys = 520 if nq in QUERY_EDGES_BY_PAIR else (nq + 2) // 3
+    shape = _shape_of_keys(B, nq, nkeys, H)
+    q, k, v = inputs.iid_qkv(B, nq, H, 64, seed=7200 + nq, device="cuda")
+    run_case(shape, q, k, v, rows=_some_rows(nq), what="%d queries" % nq)
+    _idx_case(shape, q, k, v, "%d queries" % nq)
+
+
+# Rows that leave the fast path's range, on every route that redoes them: (queries, heads, keys, width
+# of the last workgroups).  8 to 127 key tiles are redone in place, others by the second launch; from
+# 25 tiles on a sum that overflows ends the fast pass at the 24th.
+REDO = {
+    "keys": [(4096, 16, 600, 0), (2748, 16, 600, 192), (4122, 16, 600, 128),      # in place
+             (4096, 16, 2500, 0), (2748, 16, 2500, 192), (4122, 16, 2500, 128),   # in place, early
+             (4096, 16, 300, 0), (2748, 16, 300, 192), (4122, 16, 300, 128),      # second launch
+             (8448, 12, 8200, 0), (8500, 8, 8200, 128), (8560, 16, 8200, 192)],   # second launch, early
+    "list": [(4096, 16, 600, 0), (2748, 16, 600, 192), (4122, 16, 600, 128), (2748, 16, 300, 192)],
+    "dense": [(2600, 16, 2600, 192), (3700, 16, 3700, 0), (4122, 16, 4122, 128),  # in place, early
+              (8193, 16, 8193, 192), (8448, 12, 8448, 0), (8500, 8, 8500, 128)],  # second launch, early
+    # 256 pairs: 16 frames of 16 heads
+    "frame": [(768, 256, 768, 0), (700, 256, 700, 192), (1374, 256, 1374, 128),   # in place
+              (2000, 256, 2000, 0), (300, 256, 300, 0)],                          # early; second launch
+}
+
+
+def _spoil(extreme):
+    """Queries (and keys) of which some rows, or all, leave the fast path's range: `own` and `few` as
+    in test_narrow_tail_workgroups, one row in 211 or two in all; `low`: every logit near -240, so that
+    every sum is below the range and no sum overflows."""
+    def own(q, k):
+        q[:, ::211] = 32 * k[:, ::211]
+        return q, k
+
+    def few(q, k):
+        for r in (3, q.shape[1] - 2):
+            q[:, r] = 32 * k[:, r]
+        return q, k
+
+    def low(q, k):
+        u = torch.ones(64, device="cuda")
+        return (-30.0 * u).expand_as(q).to(torch.bfloat16).contiguous(), (u + 0.05 * k.float()).to(torch.bfloat16)
+
+    return {"own": own, "few": few, "low": low}[extreme]
+
+
+@pytest.mark.parametrize("extreme", ["own", "few", "low"])
+@pytest.mark.parametrize("kind,case", [(kind, c) for kind, cases in REDO.items() for c in cases])
+def test_rows_redone_on_every_route(kind, case, extreme):
+    nq, H, nkeys, width = case
+    seed = 7700 + nq + nkeys
+    if kind == "frame":
+        return _frame_case(16, nq, H // 16, seed, _spoil(extreme))
+    q, k, v = inputs.iid_qkv(1, nq, H, 64, seed=seed, device="cuda")
+    q, k = _spoil(extreme)(q, k)
+    rows = np.unique(np.concatenate([_some_rows(nq)[::2], np.arange(0, nq, 211), [3, nq - 2]]))
+    what = "%s %s %s" % (kind, case, extreme)
+    if kind == "keys":
+        shape = _shape_of_keys(1, nq, nkeys, H)
+        run_case(shape, q, k, v, rows=rows, what=what)
+        _idx_case(shape, q, k, v, what)
+    elif kind == "list":
+        shape = agg.make_shape(1, 1, 1, nq, 0, H, 64, 1, 3, 0)
+        gen = torch.Generator().manual_seed(seed)
+        lst = torch.randperm(nq, generator=gen)[:nkeys].to(torch.int32).view(1, nkeys).cuda()
+        check_list_case(shape, lst, q, k, v, rows[::2], what)
+    else:
+        shape = agg.make_shape(1, 1, 1, nq, 0, H, 64, 1, 1, 0, flags=0)
+        O, lse = harness.dense_forward(shape, q, k, v)
+        torch.cuda.synchronize()
+        want_o, want_lse = orc.dense_rows(oshape(shape), *(inputs.bf16_bits(t) for t in (q, k, v)), rows)
+        check_output(O, lse, want_o, want_lse, rows, what, q, k, shape.scale)

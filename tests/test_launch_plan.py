@@ -1,0 +1,92 @@
+"""The attention's launch plan, without a GPU: the plan is plain host code, compiled here by itself.
+
+Which kernel a call runs follows from its queries, pairs and key tiles alone.  The GPU tests name the
+kernels and widths they are for; this file checks that their sizes still lead there, so that a
+changed rule cannot quietly leave a kernel without its tests."""
+import os
+import subprocess
+
+import pytest
+
+import test_gpu_parity as parity
+import test_gpu_variants as variants
+from paper_2512_02541_amd import build as b
+
+DRIVER = r"""
+#include <stdio.h>
+#include "agg_attn_plan.h"
+int main() {
+  long long nq, npairs, tiles;
+  while (scanf("%lld %lld %lld", &nq, &npairs, &tiles) == 3) {
+    const agg::TilePlan p = agg::plan_tiles(nq, (int)npairs, tiles);
+    printf("%d %d %d %d %d %d\n", p.n_full, p.n_tail, p.tail_q, p.tails_last, p.split,
+           (int)agg::redo_in_place(tiles));
+  }
+}
+"""
+
+
+@pytest.fixture(scope="module")
+def plan(tmp_path_factory):
+    """(queries, pairs, keys) -> (kernel width of the last workgroups or "split", redone in place)"""
+    d = tmp_path_factory.mktemp("plan")
+    (d / "plan.cpp").write_text(DRIVER)
+    exe = str(d / "plan")
+    subprocess.check_call(["g++", "-std=c++17", "-O1", "-Wall", "-Werror", "-Wno-unused-function", "-I", b.CSRC,
+                           "-o", exe, str(d / "plan.cpp")])
+
+    def ask(nq, npairs, nkeys):
+        text = "%d %d %d\n" % (nq, npairs, -(-nkeys // 64))
+        out = subprocess.run([exe], input=text, text=True, check=True, stdout=subprocess.PIPE).stdout
+        n_full, n_tail, tail_q, _, split, redo = (int(x) for x in out.split())
+        # every query belongs to exactly one workgroup, and none is empty
+        last = n_tail if n_tail else n_full
+        width = tail_q if n_tail else 256
+        assert (n_full + n_tail) * npairs > 0 and (n_full == 0 or n_tail == 0 or tail_q in (128, 192))
+        assert n_full * 256 + n_tail * tail_q >= nq > n_full * 256 + n_tail * tail_q - width and last > 0
+        return "split" if split else (tail_q if n_tail else 0), bool(redo) and not split
+
+    return ask
+
+
+def test_every_query_has_a_workgroup(plan):
+    for npairs in (1, 7, 16, 20, 255, 256, 300, 5000):
+        for nq in (1, 127, 128, 129, 255, 256, 257, 1374, 4096, 10441, 54960):
+            for nkeys in (1, 64, 65, 449, 513, 8129):
+                plan(nq, npairs, nkeys)
+
+
+def test_key_sweeps_reach_their_kernels(plan):
+    for nkeys in parity.TILE_EDGE_COUNTS:
+        # one frame of two heads: shared keys from two tiles on
+        assert (plan(nkeys, 2, nkeys)[0] == "split") == (nkeys > 64), nkeys
+        redo = 8 * 64 - 63 <= nkeys < 127 * 64
+        for width, nq in variants.QUERIES_BY_WIDTH.items():
+            assert plan(nq, 16, nkeys) == (width, redo), (nkeys, width)
+        assert plan(nkeys, 33 * 8, nkeys)[0] != "split"
+        assert plan(nkeys, 33 * 8, nkeys)[1] == redo
+
+
+def test_query_sweeps_reach_their_kernels(plan):
+    for nq in variants.QUERY_EDGES:
+        assert plan(nq, 9 * 29, (nq + 2) // 3) == (0, False), nq
+    for nq, width in variants.QUERY_EDGES_BY_PAIR.items():
+        assert plan(nq, 9 * 29, 520) == (width, True), nq
+
+
+def test_redo_cases_reach_their_kernels(plan):
+    routes = set()
+    for kind, cases in variants.REDO.items():
+        for nq, npairs, nkeys, width in cases:
+            got = plan(nq, npairs, nkeys)
+            assert got == (width, 8 <= -(-nkeys // 64) < 128), (kind, nq, npairs, nkeys, got)
+            routes.add((kind, *got))
+    # compacted and index-driven: three widths, in place and by the second launch; rows in place likewise
+    assert {r for r in routes if r[0] == "keys"} == {("keys", w, r) for w in (0, 128, 192) for r in (False, True)}
+    assert {r[1:] for r in routes if r[0] in ("dense", "frame")} == {(w, r) for w in (0, 128, 192) for r in (False, True)}
+
+
+def test_tail_cases_reach_their_kernels(plan):
+    want = ["split", 192, 192, 192, 192, 192, 192, 0, 192]
+    assert [plan(nq, B * H, -(-nq // s))[0] for B, nq, H, s in variants.TAILS] == want
+    assert [plan(L, 256, L)[0] for L in (449, 600, 700, 769)] == [0, 128, 192, 128]
