@@ -279,8 +279,9 @@ def test_attention_kernel_leaves_m0_to_its_copy_statements(tmp_path):
 
 
 def test_projection_kernels_leave_m0_to_their_copy_statements(tmp_path):
-    """The same for the projection kernels, which use the same copy statement; and their waits
-    count on no scratch access between the copies: none of them may spill."""
+    """The same for the projection kernels, which use the same copy statement; and none of them may
+    spill vector registers: scratch accesses between the copies would make their counted waits longer
+    than meant.  (Scalar registers may spill, to lanes of a vector register.)"""
     import subprocess
 
     from paper_2512_02541_amd import build as b
@@ -329,3 +330,32 @@ def test_attention_kernels_that_redo_rows_do_not_spill(tmp_path):
                 spilled.append((name.group(1), field))
     assert seen == 21, "three sources, three widths with and without the redo, and the split kernels"
     assert not spilled, spilled
+
+
+def test_projection_kernels_store_as_often_as_their_waits_count(tmp_path):
+    """After a whole tile the projection kernels wait for copies that are older than the tile's stores, by
+    the number of accesses in between.  Were the compiler to merge stores, that wait would end before
+    the copies have landed: a whole tile's stores must be exactly 16 (256-wide tiles) or 8 (128-wide)
+    in one run without a branch, and a partial tile's as many, each behind its own condition."""
+    import subprocess
+
+    from paper_2512_02541_amd import build as b
+
+    out = tmp_path / "agg_block.s"
+    cmd = [b.HIPCC, *b.FLAGS, "-I", os.path.join(ROOT, "include"), "-I", b.CSRC, "-S",
+           "--cuda-device-only", os.path.join(b.CSRC, "agg_block.hip"), "-o", str(out)]
+    subprocess.check_call(cmd, stderr=subprocess.DEVNULL)
+    kernels = re.findall(r"^(\S*linear_kernelILi(\d+)E\S*):[^\n]*\n(.*?)^\.Lfunc_end", out.read_text(),
+                         flags=re.M | re.S)
+    assert len(kernels) == 4, [k[0] for k in kernels]
+    for name, edge, body in kernels:
+        instr, want = ("global_store_dwordx4", 16) if edge == "256" else ("global_store_dwordx2", 8)
+        runs, run = [], 0
+        for line in body.splitlines():
+            if re.match(r"\s+\w*store", line):
+                assert instr in line, (name, line)
+                run += 1
+            elif re.match(r"\s+s_c?branch", line) or re.match(r"\.LBB", line):
+                runs.append(run)
+                run = 0
+        assert sorted(r for r in runs if r) == [1] * want + [want], (name, runs)
