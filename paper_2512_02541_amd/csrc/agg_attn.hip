@@ -728,7 +728,7 @@ __device__ __forceinline__ bool attend(const AttnArgs& p, uint16_t* tiles, int b
   // caller's list: membership comes from a bitmap, the dropped count from device memory
   const int64_t n_drop = p.nd_dev ? (int64_t)p.nd_dev[b] : g.n_dropped;
   // ordinary and per-frame attention have no extras; where that is known at compile time the fast
-  // path's code is a third shorter (the general path's would spill: 353 registers instead of 15 in
+  // path's code is a third shorter (the general path's would spill: 353 registers instead of 16 in
   // the second launch, 149 to 192 instead of none where rows are redone in place)
   constexpr bool kExtras = kSrc != kSrcRows || kGen;
   const bool takes = kExtras && !(kSplit && group);
@@ -1027,36 +1027,42 @@ __device__ __forceinline__ uint64_t* redo_slot(const AttnArgs& p, const Work& w)
   return reinterpret_cast<uint64_t*>(p.O + (((int64_t)w.b * p.g.NQ + w.q_begin) * p.g.H + w.h) * kHeadDim);
 }
 
+// The kernel's arguments (its only parameter, at the start of its argument memory), to be read again
+// from here on: what one path derives from them is then not held for another.
+__device__ __forceinline__ const AttnArgs& args_again() {
+  typedef const __attribute__((address_space(4))) AttnArgs* KernelArgs;
+  KernelArgs args = (KernelArgs)__builtin_amdgcn_kernarg_segment_ptr();
+  asm volatile("" : "+s"(args));
+  return *(const AttnArgs*)args;
+}
+
+// blocks (of one 16-query tile) of a narrow workgroup's wavefront
+constexpr int tail_blocks(int tail_q) { return tail_q == 192 ? 3 : 2; }
+
 // kTailQ: queries of the launch's narrow workgroups (0: it has none).
 // kRedo: a workgroup redoes its own rows by the general path, 128 queries at a time, instead of
 // leaving the mark for a second launch.  At that width the general path needs no more registers
 // than the fast one, provided that nothing is held for it meanwhile: it starts from an opaque
-// thread number (attend) and reads the kernel's arguments again (they are the kernel's only
-// parameter, at the start of its argument memory).  So no instance spills, which a build test
-// checks, and each uses within 13 registers what it uses without kRedo.  Sharing both with the
-// fast path spilled 14 registers (compacted), 32 (rows) and 33 (indexed) at full width, some of
-// them in every workgroup's epilogue.
+// thread number (attend) and reads the kernel's arguments again.  So no instance spills, which a
+// build test checks, and each uses within 13 registers what it uses without kRedo.  Sharing both
+// with the fast path spilled 14 registers (compacted), 32 (rows) and 33 (indexed) at full width,
+// some of them in every workgroup's epilogue.
 template <int kSrc, int kTailQ, bool kRedo>
 __global__ __launch_bounds__(kAttnThreads, kBlocksPerCu) void sga_attn_kernel(AttnArgs p) {
   __shared__ __align__(16) uint16_t tiles[kTileLds];
   Work w;
   if (!workgroup_work(p, w)) return;
   bool done;
-  if (kTailQ != 0 && w.tail) {
-    constexpr int kTailQB = kTailQ == 192 ? 3 : 2;  // blocks of one 16-query tile
-    done = attend<kSrc, false, kTailQB, 1>(p, tiles, w.b, w.h, w.q_begin, w.q_end);
-  } else {
+  if (kTailQ != 0 && w.tail)
+    done = attend<kSrc, false, tail_blocks(kTailQ), 1>(p, tiles, w.b, w.h, w.q_begin, w.q_end);
+  else
     done = attend<kSrc, false, 2, 2>(p, tiles, w.b, w.h, w.q_begin, w.q_end);
-  }
   if (done) return;
   if (!kRedo) {
     if (threadIdx.x == 0) *redo_slot(p, w) = kRedoMark;
     return;
   }
-  typedef const __attribute__((address_space(4))) AttnArgs* KernelArgs;
-  KernelArgs args = (KernelArgs)__builtin_amdgcn_kernarg_segment_ptr();
-  asm volatile("" : "+s"(args));
-  const AttnArgs& again = *(const AttnArgs*)args;
+  const AttnArgs& again = args_again();
 #pragma unroll 1
   for (int64_t q = w.q_begin; q < w.q_end; q += kWaves * wave_queries(2, 1)) {
     __syncthreads();  // the LDS is free
@@ -1079,38 +1085,43 @@ __global__ __launch_bounds__(2 * kAttnThreads, 2) void sga_attn_split_kernel(Att
 
 // The general path is a kernel of its own, launched behind the first on the same stream: it is
 // rarely needed, starts over from the workgroup's inputs, and this way does not weigh on the
-// register allocation of the fast path.  Workgroups without the mark leave at once; narrow ones
-// are redone at full width with the queries beyond their own left out.
-template <int kSrc>
+// register allocation of the fast path.  Workgroups without the mark leave at once; narrow ones are
+// redone at their own width.  (At full width, with the queries beyond their own left out, calls of
+// which every workgroup is redone took, us, then / now, and with full-width workgroups alone in both
+// launches: ordinary attention, 12 frames of 37x37 2013 / 1610, 1835; 10 frames of 28x37, 8 heads
+// 398 / 301, 398; compacted, 25 frames 2927 / 2739, 2990.)
+template <int kSrc, int kTailQ>
 __global__ __launch_bounds__(kAttnThreads, kBlocksPerCu) void sga_attn_general_kernel(AttnArgs p) {
   __shared__ __align__(16) uint16_t tiles[kTileLds];
   Work w;
   if (!workgroup_work(p, w)) return;
   if (*redo_slot(p, w) != kRedoMark) return;  // same value in every lane
   __syncthreads();  // every wavefront has read the mark before any of them overwrites it
-  attend<kSrc, true, 2, 2>(p, tiles, w.b, w.h, w.q_begin, w.q_end);
+  if (kTailQ != 0 && w.tail)
+    attend<kSrc, true, tail_blocks(kTailQ), 1>(args_again(), tiles, w.b, w.h, w.q_begin, w.q_end);
+  else
+    attend<kSrc, true, 2, 2>(p, tiles, w.b, w.h, w.q_begin, w.q_end);
 }
 
-template <int kSrc, bool kRedo>
-static void launch_fast(const AttnArgs& p, dim3 grid, hipStream_t st) {
+template <int kSrc, int kTailQ>
+static void launch_both(const AttnArgs& p, dim3 grid, hipStream_t st) {
   const dim3 block(kAttnThreads);
-  const int tail_q = p.plan.n_tail ? p.plan.tail_q : 0;
-  if (tail_q == 0) hipLaunchKernelGGL((sga_attn_kernel<kSrc, 0, kRedo>), grid, block, 0, st, p);
-  else if (tail_q == 192) hipLaunchKernelGGL((sga_attn_kernel<kSrc, 192, kRedo>), grid, block, 0, st, p);
-  else hipLaunchKernelGGL((sga_attn_kernel<kSrc, 128, kRedo>), grid, block, 0, st, p);
+  if (redo_in_place(p.g.M_pad / kTileRows)) {
+    hipLaunchKernelGGL((sga_attn_kernel<kSrc, kTailQ, true>), grid, block, 0, st, p);
+  } else {
+    hipLaunchKernelGGL((sga_attn_kernel<kSrc, kTailQ, false>), grid, block, 0, st, p);
+    hipLaunchKernelGGL((sga_attn_general_kernel<kSrc, kTailQ>), grid, block, 0, st, p);
+  }
 }
 
 template <int kSrc>
 static void launch_source(const AttnArgs& p, hipStream_t st) {
   const dim3 grid((unsigned)(first_list(p.plan, p.npairs).groups + second_list(p.plan, p.npairs).groups));
-  if (p.plan.split) {
-    hipLaunchKernelGGL(sga_attn_split_kernel<kSrc>, grid, dim3(2 * kAttnThreads), 0, st, p);
-  } else if (redo_in_place(p.g.M_pad / kTileRows)) {
-    launch_fast<kSrc, true>(p, grid, st);
-  } else {
-    launch_fast<kSrc, false>(p, grid, st);
-    hipLaunchKernelGGL(sga_attn_general_kernel<kSrc>, grid, dim3(kAttnThreads), 0, st, p);
-  }
+  const int tail_q = p.plan.n_tail ? p.plan.tail_q : 0;
+  if (p.plan.split) hipLaunchKernelGGL(sga_attn_split_kernel<kSrc>, grid, dim3(2 * kAttnThreads), 0, st, p);
+  else if (tail_q == 0) launch_both<kSrc, 0>(p, grid, st);
+  else if (tail_q == 192) launch_both<kSrc, 192>(p, grid, st);
+  else launch_both<kSrc, 128>(p, grid, st);
 }
 
 hipError_t launch_attn(const Geom& g, uint32_t flags, float scale, float mean_bias, const void* Q,

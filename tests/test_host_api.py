@@ -310,7 +310,7 @@ def test_projection_kernels_leave_m0_to_their_copy_statements(tmp_path):
 def test_attention_kernels_that_redo_rows_do_not_spill(tmp_path):
     """The attention kernels that redo rows themselves hold two paths' code; nothing of the second may
     lie in scratch memory while the first runs, or every workgroup pays for it.  (The kernel of the
-    second launch, which only ever runs the general path at full width, does spill.)"""
+    second launch, whose general path is as wide as the fast one, does spill.)"""
     import subprocess
 
     from paper_2512_02541_amd import build as b
