@@ -20,6 +20,10 @@
  *   - `hip_stream` is a hipStream_t passed as void* (NULL = the default stream).
  *     Every call only enqueues work on that stream: no allocation, no
  *     synchronisation, no retained pointers.  The caller owns every buffer.
+ *   - Results are bit-reproducible from run to run for the same shape.  Sums are formed in an order
+ *     that may depend on the shape as a whole: the last bits of one row of O or lse may differ
+ *     between calls that hold it with other numbers of queries, batch elements or heads, and those
+ *     of kmean and vmean between calls with other B or H.  The error is the same.
  *   - Return value: AGG_OK or a negative agg_status.  All argument validation
  *     happens before the first launch, so every error except AGG_ERR_LAUNCH is
  *     reported without touching the GPU.  Faults inside a kernel surface at the

@@ -34,9 +34,10 @@ struct TilePlan {
 // tail that the cost model below puts at least 1.5 % ahead of full-width workgroups alone.
 // Measured with it: 10 frames of 37x37 patches, 16 heads, 367 us instead of 401 (attention
 // alone); two frames of 16x16 patches 27.6 instead of 33.3 (the whole layer).  The model knows
-// neither the key source nor the number of keys; over 64 launches of all three sources with 8 to
-// 122 key tiles, 8 to 32 heads and 1 to 300 frames the plan took 0.60 to 1.00 of what full-width
-// workgroups alone, dealt out a whole pair per XCD, take.
+// neither the key source nor the number of keys: over 120 random launches for which it takes narrow
+// workgroups (all three sources, 10 to 670 key tiles, 4 to 32 heads, 1 to 73 frames) they took 0.69 to
+// 1.03 of full-width ones alone, half of them under 0.91; the worst are 53 frames of 16x16 through
+// the index list with 20 heads, 474 / 462 us, and per-frame attention, 16 frames of 28x37, 79 / 77.
 struct TileCost {
   int queries;
   double paired, alone;  // on a CU that holds two workgroups / this one only

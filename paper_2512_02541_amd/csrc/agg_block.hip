@@ -403,9 +403,11 @@ static hipError_t launch_linear_tiles(const uint16_t* A, const LinearOuts& outs,
   return hipGetLastError();
 }
 
-// Times of a launch in microseconds, from what a round of tiles took at K = 1024 (which they
-// follow): 256-wide tiles 33, one to a CU; 128-wide ones 20.6 two to a CU and 14 alone, 7 where a
-// CU's last one runs alone behind others.
+// Times of a launch in microseconds, from what a round of tiles took at K = 1024: 256-wide tiles 33,
+// one to a CU; 128-wide ones 20.6 two to a CU and 14 alone, 7 where a CU's last one runs alone behind
+// others.  They are taken to follow K, which stores and starts do not; at K = 128 to 4096 and 261 to
+// 137 400 rows (184 launches) the choice below took 0.85 to 1.03 of the better single size, once 1.07
+// (K = 512, 21 984 rows, three matrices: 46.3 against 43.4 us with small tiles alone).
 static double linear_time(int64_t rows, int edge, int N, int K, int count) {
   const int64_t tiles = (rows + edge - 1) / edge * ((N + edge - 1) / edge) * count;
   const int64_t mine = (tiles + kGemmXcds - 1) / kGemmXcds;  // of one XCD, which has 32 CUs

@@ -119,7 +119,8 @@ __device__ inline void gather_tile(const Geom& g, const uint16_t* __restrict__ K
     *reinterpret_cast<u32x4*>(&s.v[hl * kVHead + row * kVPad + j * 8]) = vv;
   };
   if (!kPool && nheads == kHeadGroup) {
-    // all of a thread's reads before any of them is used
+    // All of a thread's reads before any of them is used.  The call, us, one at a time / as it is,
+    // medians of 41 alternating runs: 300 frames 441 / 425, 800 frames 932 / 918.
     constexpr int kReads = kTileRows * kHeadGroup * 8 / kSubThreads;
     u32x4 kv[kReads], vv[kReads];
 #pragma unroll
@@ -230,7 +231,7 @@ static MeanPlan mean_plan(const Geom& g) {
   // number stay as they are.  With whole rows a workgroup's 512 of them, two at a time, took 40 us
   // however short the sequence.  The call, us, whole rows / 256 / 512 / 1024 workgroups: 2 frames of
   // 37x37 44 / 12 / 12 / 12; 10 frames 46 / 18.5 / 18.5 / 18.5; 20 frames 67 / 30 / 33 / 33; 40 frames
-  // 75 / 57 / 59 / 64; 100 frames 176 / 170 / 173 / 174; 300 frames 443 / 427 (not split).
+  // 75 / 57 / 59 / 64; 100 frames 176 / 170 / 173 / 174.
   constexpr int kMeanFill = 256;
   int heads = g.H < kSubThreads / 8 ? g.H : kSubThreads / 8;
   while (heads > 1 && (int64_t)p.nchunks * ((g.H + heads - 1) / heads) * g.B < kMeanFill)
