@@ -497,7 +497,7 @@ def main():
 
     block = None
     if not args.no_block:
-        # BASELINE config 5: 12 global blocks at 333 frames, the first 4 as frame attention
+        # 12 global blocks at 333 frames, the first 4 as frame attention
         block = time_block_stack("f333", 12, 4, None, 2, 1, False, log)
         torch.cuda.empty_cache()
 

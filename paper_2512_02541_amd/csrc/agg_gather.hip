@@ -120,7 +120,7 @@ __device__ inline void gather_tile(const Geom& g, const uint16_t* __restrict__ K
   };
   if (!kPool && nheads == kHeadGroup) {
     // All of a thread's reads before any of them is used.  The call, us, one at a time / as it is,
-    // medians of 41 alternating runs: 300 frames 441 / 425, 800 frames 932 / 918.
+    // medians of 41 alternating runs: 100 frames 183 / 172, 300 frames 440 / 424, 800 frames 931 / 917.
     constexpr int kReads = kTileRows * kHeadGroup * 8 / kSubThreads;
     u32x4 kv[kReads], vv[kReads];
 #pragma unroll
