@@ -81,8 +81,10 @@ static inline TilePlan plan_tiles(int64_t NQ, int npairs, int64_t key_tiles) {
   if (npairs * NQ > INT32_MAX) return best;  // far past the sizes at which a tail matters
   // With at least a pair per CU the rounds are many, and what is left to gain are the queries
   // that do not exist; the tails then follow their pair's other tiles, whose keys they share.
-  // Per-frame attention, 90 frames of 37x37 patches: 710 us instead of 728.  Under eight key tiles
-  // the second code path costs more than the idle queries: 50 frames of 16x16, 51.0 against 50.2.
+  // Per-frame attention, 90 frames of 37x37 patches: 710 us instead of 728.  Under eight key tiles they
+  // are left out: while such launches had a second one behind them, 50 frames of 16x16 took 51.0 us
+  // with them and 50.2 without.  (Now that they redo rows in place it is 42.6 and 43.5; 300 frames of
+  // 5x10 37.2 and 49.1.)
   const bool by_pair = npairs >= kCus;
   if (by_pair && key_tiles < 8) return best;
   double least = by_pair ? (double)best.n_full : launch_time(npairs * (int64_t)best.n_full, 0, kFullCost);
@@ -105,23 +107,26 @@ static inline TilePlan plan_tiles(int64_t NQ, int npairs, int64_t key_tiles) {
   return best;
 }
 
-// Whether a launch of whole (not split) workgroups redoes rows itself, without a second launch.
+// Whether a launch that is not split redoes rows itself, without a second launch.
 //
-// An idle second launch is 1 to 4 % of a call with few key tiles, and where one query needs the
-// general path the others no longer wait for it.  Under eight tiles the larger kernel costs more
-// (50 frames of 16x16, 5 tiles: 47 / 53 us), and with long key loops the idle launch is lost in
-// them.  Attention alone, us, second launch / redo in place, by the width of the last workgroups:
-//   full  compacted, 12 frames of 16x16, 16 tiles          26.5 / 24.8
-//         compacted, 3 frames of 37x37, 12 heads, 44 tiles 50.9 / 48.9;  5 frames, 66 tiles 114.3 / 112.2
-//         compacted, 30 frames, 12 heads, 101 tiles         661 / 658
-//         indexed, 12 frames of 16x16, 16 tiles            27.5 / 26.0;  5 frames, 45 tiles 87.8 / 86.0
-//         rows, per-frame, 5 frames, 22 tiles 44.1 / 42.1;  5 frames, 108 tiles 172.8 / 170.5
-//   192   compacted, 2 frames, 33 tiles 33.5 / 32.0;  10 frames, 122 tiles 330.7 / 327.9
-//         indexed, 10 frames 353.9 / 351.0;  rows, 2 frames, 43 tiles 38.2 / 36.7
-//   128   compacted, 3 frames, 44 tiles 55.4 / 53.9;  rows, per-frame, 90 frames, 22 tiles 689 / 665
-// One query out of range / every workgroup: compacted, 10 frames 576 / 355 and 571 / 607 (the one
-// loss: 128 queries at a time read the keys twice); rows, 5 frames, 108 tiles 378 / 233 and
-// 285 / 291; per-frame, 90 frames 738 / 683 and 1894 / 1580.
-static inline bool redo_in_place(int64_t key_tiles) { return key_tiles >= 8 && key_tiles < 128; }
+// An idle second launch is 1 to 18 % of a call with few key tiles, and where one query needs the
+// general path the others no longer wait for it; with long key loops the idle launch is lost in
+// them, and there redoing everything 128 queries at a time, which reads the keys twice, costs more.
+// Attention alone, us, second launch / redo in place, by the width of the last workgroups:
+//   full  rows, per-frame, 300 frames of 5x10, 1 tile 57.4 / 48.7;  50 frames of 16x16, 5 tiles 47.7 / 43.4;
+//         5 frames of 37x37, 22 tiles 43.1 / 41.0;  ordinary, 5 frames, 108 tiles 170.0 / 167.9
+//         compacted, 30 frames of 16x16, 3 tiles 28.3 / 26.3;  12 frames, 16 tiles 26.7 / 24.9;  3 frames of
+//         37x37, 12 heads, 44 tiles 51.0 / 49.0;  30 frames, 12 heads, 101 tiles 670 / 656
+//         indexed, 12 frames of 16x16, 16 tiles 27.5 / 26.0;  5 frames of 37x37, 45 tiles 88.1 / 86.2
+//   192   compacted, 20 frames of 16x16, 3 tiles 21.9 / 19.8;  2 frames of 37x37, 33 tiles 34.1 / 32.5;
+//         10 frames, 122 tiles 353 / 350;  indexed, 10 frames 379 / 376;  rows, 2 frames, 43 tiles 37.8 / 35.7
+//         (beyond the line: compacted, 12 frames, 133 tiles 488.5 / 485.0;  20 frames, 222 tiles 1254 / 1252)
+//   128   compacted, 9 frames, 1 tile 43.5 / 40.9;  3 frames, 44 tiles 55.6 / 53.7;
+//         rows, per-frame, 90 frames, 22 tiles 667 / 665;  300 frames of 24x24, 10 tiles 564 / 541
+// One query out of range / every workgroup: compacted, 10 frames of 37x37 573 / 351 and 512 / 596, the
+// largest loss; indexed, 8 frames of 16x16, 20 heads 33.2 / 36.1 and 32.7 / 36.5; rows, ordinary, 5 frames
+// 373 / 231 and 284 / 288; per-frame, 90 frames 737 / 654 and 1629 / 1515; 50 frames of 16x16 64.6 / 43.5
+// and 118.8 / 102.5.
+static inline bool redo_in_place(int64_t key_tiles) { return key_tiles < 128; }
 
 }  // namespace agg

@@ -33,7 +33,7 @@ TAILS = [
     (1, 24984, 12, 301),   # ... over pairs that share the XCDs
     (1, 8193, 16, 97),     # narrow workgroups only (192), the last of 129 queries
     (2, 2049, 8, 31),      # two batch elements
-    # eight key tiles and more: rows that leave the fast path's range are redone by the same launch
+    # nine key tiles
     (1, 2600, 16, 5),
     (1, 4096, 16, 8),      # full-width workgroups only
     (1, 13740, 16, 27),
@@ -214,19 +214,20 @@ def test_query_counts_of_four_wavefront_kernels(nq):
 
 
 # Rows that leave the fast path's range, on every route that redoes them: (queries, heads, keys, width
-# of the last workgroups).  8 to 127 key tiles are redone in place, others by the second launch; from
-# 25 tiles on a sum that overflows ends the fast pass at the 24th.
+# of the last workgroups).  Up to 127 key tiles they are redone in place, beyond that by the second
+# launch; from 25 tiles on a sum that overflows ends the fast pass at the 24th.
 REDO = {
-    "keys": [(4096, 16, 600, 0), (2748, 16, 600, 192), (4122, 16, 600, 128),      # in place
+    "keys": [(4096, 16, 30, 0), (2748, 16, 300, 192), (4122, 16, 300, 128),       # in place
+             (4096, 16, 600, 0), (2748, 16, 600, 192), (4122, 16, 600, 128),
              (4096, 16, 2500, 0), (2748, 16, 2500, 192), (4122, 16, 2500, 128),   # in place, early
-             (4096, 16, 300, 0), (2748, 16, 300, 192), (4122, 16, 300, 128),      # second launch
              (8448, 12, 8200, 0), (8500, 8, 8200, 128), (8560, 16, 8200, 192)],   # second launch, early
-    "list": [(4096, 16, 600, 0), (2748, 16, 600, 192), (4122, 16, 600, 128), (2748, 16, 300, 192)],
+    "list": [(2748, 16, 300, 192), (4096, 16, 600, 0), (2748, 16, 600, 192), (4122, 16, 600, 128),
+             (4096, 16, 8200, 0), (2748, 16, 8200, 192), (4122, 16, 8200, 128)],
     "dense": [(2600, 16, 2600, 192), (3700, 16, 3700, 0), (4122, 16, 4122, 128),  # in place, early
               (8193, 16, 8193, 192), (8448, 12, 8448, 0), (8500, 8, 8500, 128)],  # second launch, early
     # 256 pairs: 16 frames of 16 heads
-    "frame": [(768, 256, 768, 0), (700, 256, 700, 192), (1374, 256, 1374, 128),   # in place
-              (2000, 256, 2000, 0), (300, 256, 300, 0)],                          # early; second launch
+    "frame": [(50, 256, 50, 0), (300, 256, 300, 0), (768, 256, 768, 0), (700, 256, 700, 192),
+              (1374, 256, 1374, 128), (2000, 256, 2000, 0)],                      # in place
 }
 
 
@@ -268,7 +269,9 @@ def test_rows_redone_on_every_route(kind, case, extreme):
     elif kind == "list":
         shape = agg.make_shape(1, 1, 1, nq, 0, H, 64, 1, 3, 0)
         gen = torch.Generator().manual_seed(seed)
-        lst = torch.randperm(nq, generator=gen)[:nkeys].to(torch.int32).view(1, nkeys).cuda()
+        # (a list longer than the sequence names tokens more than once)
+        lst = torch.cat([torch.randperm(nq, generator=gen) for _ in range(-(-nkeys // nq))])
+        lst = lst[:nkeys].to(torch.int32).view(1, nkeys).cuda()
         check_list_case(shape, lst, q, k, v, rows[::2], what)
     else:
         shape = agg.make_shape(1, 1, 1, nq, 0, H, 64, 1, 1, 0, flags=0)

@@ -60,16 +60,16 @@ def test_key_sweeps_reach_their_kernels(plan):
     for nkeys in parity.TILE_EDGE_COUNTS:
         # one frame of two heads: shared keys from two tiles on
         assert (plan(nkeys, 2, nkeys)[0] == "split") == (nkeys > 64), nkeys
-        redo = 8 * 64 - 63 <= nkeys < 127 * 64
+        redo = nkeys <= 127 * 64
         for width, nq in variants.QUERIES_BY_WIDTH.items():
             assert plan(nq, 16, nkeys) == (width, redo), (nkeys, width)
         assert plan(nkeys, 33 * 8, nkeys)[0] != "split"
-        assert plan(nkeys, 33 * 8, nkeys)[1] == redo
+        assert plan(nkeys, 33 * 8, nkeys)[1] == redo, nkeys
 
 
 def test_query_sweeps_reach_their_kernels(plan):
     for nq in variants.QUERY_EDGES:
-        assert plan(nq, 9 * 29, (nq + 2) // 3) == (0, False), nq
+        assert plan(nq, 9 * 29, (nq + 2) // 3) == (0, True), nq
     for nq, width in variants.QUERY_EDGES_BY_PAIR.items():
         assert plan(nq, 9 * 29, 520) == (width, True), nq
 
@@ -79,10 +79,11 @@ def test_redo_cases_reach_their_kernels(plan):
     for kind, cases in variants.REDO.items():
         for nq, npairs, nkeys, width in cases:
             got = plan(nq, npairs, nkeys)
-            assert got == (width, 8 <= -(-nkeys // 64) < 128), (kind, nq, npairs, nkeys, got)
+            assert got == (width, nkeys <= 127 * 64), (kind, nq, npairs, nkeys, got)
             routes.add((kind, *got))
     # compacted and index-driven: three widths, in place and by the second launch; rows in place likewise
-    assert {r for r in routes if r[0] == "keys"} == {("keys", w, r) for w in (0, 128, 192) for r in (False, True)}
+    for kind in ("keys", "list"):
+        assert {r for r in routes if r[0] == kind} == {(kind, w, r) for w in (0, 128, 192) for r in (False, True)}
     assert {r[1:] for r in routes if r[0] in ("dense", "frame")} == {(w, r) for w in (0, 128, 192) for r in (False, True)}
 
 
