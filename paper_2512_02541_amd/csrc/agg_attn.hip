@@ -322,9 +322,11 @@ struct TileCopier {
   const uint16_t *knext, *vnext;  // compact, rows: where the next tile to be copied starts
   int64_t tnext;                  // its number (tiles are copied in order)
   uint32_t wbase;          // LDS byte address of this wavefront's first slot in buffer 0
-  uint32_t vk[2], vv[2];   // byte offset of this lane's two chunks from the tile's (rows, compact)
-                           // or the row's (indexed) start, for K and for V
-  uint32_t row[2];         // row of the tile this lane's slots belong to (rows)
+  // byte offset of this lane's first chunk from the tile's (rows, compact) or the row's (indexed)
+  // start, for K and for V; the second lies half a tile (32 rows, whose swizzle is that of the first 32)
+  // further on
+  uint32_t vk, vv;
+  uint32_t row;            // row of the tile this lane's first slot belongs to (rows)
   // Indexed: an instruction's eight rows and a tile's two instructions make 16 ids per wavefront.
   // Lane l holds the id of row l % 16 of them; byte offsets are worked out once per row and handed
   // to the eight lanes that fetch it, a tile ahead of their use.  (Every lane reading and scaling
@@ -342,26 +344,23 @@ struct TileCopier {
     tnext = 0;
     const uint32_t lds0 = (uint32_t)(uintptr_t)((lds_char*)lds);
     wbase = __builtin_amdgcn_readfirstlane(lds0 + (uint32_t)wave * 1024u);
-#pragma unroll
-    for (int hh = 0; hh < 2; ++hh) {
-      const uint32_t slot = (uint32_t)tid + hh * kAttnThreads;  // 0 .. 511
-      row[hh] = slot >> 3;
-      const uint32_t c = slot & 7;
-      const uint32_t ck = (c ^ k_swizzle(row[hh])) * 16u;
-      const uint32_t cv = (c ^ (4u * ((row[hh] >> 1) & 1))) * 16u;
-      if (kSrc == kSrcCompact) {
-        // K: the LDS slot of a key has bits 3 and 4 of the key number exchanged (frag_addr)
-        const uint32_t key = slot & 31u;
-        const uint32_t swapped = (key & 7u) | ((key & 8u) << 1) | ((key & 16u) >> 1);
-        vk[hh] = ((slot & ~31u) | swapped) * 16u;
-        vv[hh] = slot * 16u;
-      } else if (kSrc == kSrcRows) {
-        vk[hh] = row[hh] * s.row_bytes + ck;
-        vv[hh] = row[hh] * s.row_bytes + cv;
-      } else {
-        vk[hh] = ck;
-        vv[hh] = cv;
-      }
+    const uint32_t slot = (uint32_t)tid;  // 0 .. 255, and 256 more
+    row = slot >> 3;
+    const uint32_t c = slot & 7;
+    const uint32_t ck = (c ^ k_swizzle(row)) * 16u;
+    const uint32_t cv = (c ^ (4u * ((row >> 1) & 1))) * 16u;
+    if (kSrc == kSrcCompact) {
+      // K: the LDS slot of a key has bits 3 and 4 of the key number exchanged (frag_addr)
+      const uint32_t key = slot & 31u;
+      const uint32_t swapped = (key & 7u) | ((key & 8u) << 1) | ((key & 16u) >> 1);
+      vk = ((slot & ~31u) | swapped) * 16u;
+      vv = slot * 16u;
+    } else if (kSrc == kSrcRows) {
+      vk = row * s.row_bytes + ck;
+      vv = row * s.row_bytes + cv;
+    } else {
+      vk = ck;
+      vv = cv;
     }
     if (kSrc == kSrcIndexed) {
       lane = tid & 63;
@@ -388,39 +387,41 @@ struct TileCopier {
   __device__ __forceinline__ void issue(int buf) {
     const uint32_t mk = wbase + (uint32_t)buf * (kChunks * 16);
     const uint32_t mv = wbase + (uint32_t)(kLdsTiles + buf) * (kChunks * 16);
-    constexpr int kInstr = kAttnThreads < kChunks ? 2 : 1;
+    static_assert(2 * kAttnThreads == kChunks, "two copies per thread and tile");
     if (kSrc == kSrcCompact) {
 #pragma unroll
-      for (int hh = 0; hh < kInstr; ++hh) {
-        dma16(knext, vk[hh], mk + hh * kAttnThreads * 16);
-        dma16(vnext, vv[hh], mv + hh * kAttnThreads * 16);
+      for (int hh = 0; hh < 2; ++hh) {
+        dma16(knext + hh * (kTileElems / 2), vk, mk + hh * kAttnThreads * 16);
+        dma16(vnext + hh * (kTileElems / 2), vv, mv + hh * kAttnThreads * 16);
       }
       knext += kTileElems;
       vnext += kTileElems;
     } else if (kSrc == kSrcRows) {
       // the tile's rows follow each other in memory
+      const size_t half = (size_t)(kTileRows / 2) * (src.row_bytes / 2);
       if ((tnext + 1) * kTileRows <= src.rows) {
 #pragma unroll
-        for (int hh = 0; hh < kInstr; ++hh) {
-          dma16(knext, vk[hh], mk + hh * kAttnThreads * 16);
-          dma16(vnext, vv[hh], mv + hh * kAttnThreads * 16);
+        for (int hh = 0; hh < 2; ++hh) {
+          dma16(knext + hh * half, vk, mk + hh * kAttnThreads * 16);
+          dma16(vnext + hh * half, vv, mv + hh * kAttnThreads * 16);
         }
       } else {  // last, partial tile: rows past the end repeat the last one; masked later
         const uint32_t last = (uint32_t)(src.rows - 1 - tnext * kTileRows);
 #pragma unroll
-        for (int hh = 0; hh < kInstr; ++hh) {
-          const uint32_t back = row[hh] > last ? (row[hh] - last) * src.row_bytes : 0u;
-          dma16(knext, vk[hh] - back, mk + hh * kAttnThreads * 16);
-          dma16(vnext, vv[hh] - back, mv + hh * kAttnThreads * 16);
+        for (int hh = 0; hh < 2; ++hh) {
+          const uint32_t r = row + hh * (kTileRows / 2);
+          const uint32_t at = (min(r, last) - row) * src.row_bytes;  // (wraps where the row is before this lane's)
+          dma16(knext, vk + at, mk + hh * kAttnThreads * 16);
+          dma16(vnext, vv + at, mv + hh * kAttnThreads * 16);
         }
       }
-      knext += (size_t)kTileRows * (src.row_bytes / 2);
-      vnext += (size_t)kTileRows * (src.row_bytes / 2);
+      knext += 2 * half;
+      vnext += 2 * half;
     } else {
 #pragma unroll
-      for (int hh = 0; hh < kInstr; ++hh) {
-        dma16(src.k, from[hh] + vk[hh], mk + hh * kAttnThreads * 16);
-        dma16(src.v, from[hh] + vv[hh], mv + hh * kAttnThreads * 16);
+      for (int hh = 0; hh < 2; ++hh) {
+        dma16(src.k, from[hh] + vk, mk + hh * kAttnThreads * 16);
+        dma16(src.v, from[hh] + vv, mv + hh * kAttnThreads * 16);
       }
       spread_ids();  // the next tile's offsets; its ids came with the last wait
       fetch_ids();                   // and the ids after those
@@ -754,33 +755,85 @@ __device__ __forceinline__ bool attend(const AttnArgs& p, uint16_t* tiles, int b
     const int64_t qc = q < q_end ? q : q_end - 1;  // tail rows recompute the last query, never stored
     return (((int64_t)b * g.NQ + qc) * g.H + h) * kHeadDim;
   };
+  // this lane's channels 16 dt + 4 G .. + 3 of the query's own value and of the mean value
+  auto load_own_v = [&](int qb, int j, int dt) {
+    return *reinterpret_cast<const u32x2*>(p.V + row_base(qb, j) + 16 * dt + 4 * G);
+  };
+  auto load_mean_v = [&](int dt) {
+    const float* vm = p.vmean + ((int64_t)b * g.H + h) * kHeadDim;
+    return *reinterpret_cast<const f32x4*>(vm + 16 * dt + 4 * G);
+  };
 
   // ---- Q fragments and the logits of the extras ----
-  // a lane holds channels 32 h + 8 G .. + 7 (h = 0, 1) of its query: the four lanes c + 16 G
-  // share the channel range
+  // A lane holds channels 32 h + 8 G .. + 7 (h = 0, 1) of its query: the four lanes c + 16 G
+  // share the channel range.  Everything is requested before anything is used, and one lane per
+  // query works out whether that was dropped: with a tile's loads behind the previous tile's
+  // arithmetic, and every lane dividing for each of its tiles, a workgroup spent 14 us here before its
+  // first key in a layer of 10 frames (now 8.5; 363 us a call instead of 370), 3.8 in one of two frames of
+  // 16x16 (2.6; 14.5 instead of 15.1).
+#pragma unroll
+  for (int qb = 0; qb < kQB; ++qb)
+#pragma unroll
+    for (int j = 0; j < kJ; ++j)
+#pragma unroll
+      for (int hh = 0; hh < 2; ++hh)
+        w.Qf[qb][2 * j + hh].u = *reinterpret_cast<const u32x4*>(p.Q + row_base(qb, j) + hh * 32 + G * 8);
+  uint64_t drop_mask = 0;  // bit i: query q_wave + i was dropped
+  if (use_diag) {
+    const int64_t q = q_wave + lane;
+    bool d = false;
+    if (lane < kWaveQ && q < q_end)
+      d = kbits ? ((kbits[q >> 5] >> (q & 31)) & 1u) == 0u : (bool)token_is_dropped(g, q);
+    drop_mask = __builtin_amdgcn_ballot_w64(d);
+  }
+  // the query's own key and value, the mean pair (general path: the values only once the row's
+  // reference is known, its registers being scarcer)
+  u32x4 own_k[kQB][kJ][2];
+  u32x2 own_v[kQB][kJ][4];
+  f32x4 mean_k[4], mean_v[4];
 #pragma unroll
   for (int qb = 0; qb < kQB; ++qb)
 #pragma unroll
     for (int j = 0; j < kJ; ++j) {
-      const int64_t q = q_wave + (qb * kJ + j) * 16 + c;
-      const int64_t qbase = row_base(qb, j);
+      dropped[qb][j] = (drop_mask >> (16 * (qb * kJ + j) + c)) & 1u;
+#pragma unroll
+      for (int hh = 0; hh < 2; ++hh) own_k[qb][j][hh] = u32x4{0u, 0u, 0u, 0u};
+#pragma unroll
+      for (int dt = 0; dt < 4; ++dt) own_v[qb][j][dt] = u32x2{0u, 0u};
+      if (kExtras && dropped[qb][j]) {
+#pragma unroll
+        for (int hh = 0; hh < 2; ++hh)
+          own_k[qb][j][hh] = *reinterpret_cast<const u32x4*>(p.K + row_base(qb, j) + hh * 32 + G * 8);
+        if (!kGen) {
+#pragma unroll
+          for (int dt = 0; dt < 4; ++dt) own_v[qb][j][dt] = load_own_v(qb, j, dt);
+        }
+      }
+    }
+  if (kExtras && use_mean) {
+    const float* km = p.kmean + ((int64_t)b * g.H + h) * kHeadDim;
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      mean_k[i] = *reinterpret_cast<const f32x4*>(km + (i >> 1) * 32 + G * 8 + 4 * (i & 1));
+      if (!kGen) mean_v[i] = load_mean_v(i);
+    }
+  }
+#pragma unroll
+  for (int qb = 0; qb < kQB; ++qb)
+#pragma unroll
+    for (int j = 0; j < kJ; ++j) {
 #pragma unroll
       for (int hh = 0; hh < 2; ++hh) {
-        u32x4 raw = *reinterpret_cast<const u32x4*>(p.Q + qbase + hh * 32 + G * 8);
+        const u32x4 raw = w.Qf[qb][2 * j + hh].u;
 #pragma unroll
         for (int i = 0; i < 4; ++i)
           w.Qf[qb][2 * j + hh].u[i] =
               pack_bf16(bf16_lo(raw[i]) * p.qscale, bf16_hi(raw[i]) * p.qscale);
       }
-      dropped[qb][j] =
-          use_diag && q < q_end &&
-          (kbits ? ((kbits[q >> 5] >> (q & 31)) & 1u) == 0u : (bool)token_is_dropped(g, q));
       float dot_self = 0.f, dot_mean = 0.f;
       if (use_mean || use_diag) {
-        const float* km = p.kmean + ((int64_t)b * g.H + h) * kHeadDim;
 #pragma unroll
         for (int hh = 0; hh < 2; ++hh) {
-          const int d0 = hh * 32 + G * 8;
           float qv[8];
 #pragma unroll
           for (int i = 0; i < 4; ++i) {
@@ -788,13 +841,11 @@ __device__ __forceinline__ bool attend(const AttnArgs& p, uint16_t* tiles, int b
             qv[2 * i + 1] = bf16_hi(w.Qf[qb][2 * j + hh].u[i]);
           }
           if (use_mean) {
-            f32x4 c0 = *reinterpret_cast<const f32x4*>(km + d0);
-            f32x4 c1 = *reinterpret_cast<const f32x4*>(km + d0 + 4);
 #pragma unroll
-            for (int i = 0; i < 4; ++i) dot_mean += qv[i] * c0[i] + qv[4 + i] * c1[i];
+            for (int i = 0; i < 4; ++i) dot_mean += qv[i] * mean_k[2 * hh][i] + qv[4 + i] * mean_k[2 * hh + 1][i];
           }
-          if (dropped[qb][j]) {
-            u32x4 kr = *reinterpret_cast<const u32x4*>(p.K + qbase + d0);
+          if (use_diag) {
+            const u32x4 kr = own_k[qb][j][hh];
 #pragma unroll
             for (int i = 0; i < 4; ++i)
               dot_self += qv[2 * i] * bf16_lo(kr[i]) + qv[2 * i + 1] * bf16_hi(kr[i]);
@@ -814,18 +865,12 @@ __device__ __forceinline__ bool attend(const AttnArgs& p, uint16_t* tiles, int b
     const float l0 = w_self + w_mean;
     if (kGen) w.la[qb][j] = (G == 0) ? l0 : 0.f;  // four lanes split a row's sum
     else w.L[qb][j] = f32x4{l0, 0.f, 0.f, 0.f};
-    const int64_t qbase = row_base(qb, j);
-    const float* vm = p.vmean + ((int64_t)b * g.H + h) * kHeadDim;
 #pragma unroll
     for (int dt = 0; dt < 4; ++dt) {
-      const int d0 = 16 * dt + 4 * G;
       f32x4 acc = {0.f, 0.f, 0.f, 0.f};
-      if (use_mean) {
-        f32x4 mv = *reinterpret_cast<const f32x4*>(vm + d0);
-        acc = mv * w_mean;
-      }
+      if (use_mean) acc = (kGen ? load_mean_v(dt) : mean_v[dt]) * w_mean;
       if (dropped[qb][j]) {
-        u32x2 vr = *reinterpret_cast<const u32x2*>(p.V + qbase + d0);
+        const u32x2 vr = kGen ? load_own_v(qb, j, dt) : own_v[qb][j][dt];
         acc[0] += w_self * bf16_lo(vr[0]);
         acc[1] += w_self * bf16_hi(vr[0]);
         acc[2] += w_self * bf16_lo(vr[1]);
@@ -923,6 +968,11 @@ __device__ __forceinline__ bool attend(const AttnArgs& p, uint16_t* tiles, int b
   // (now idle) K/V LDS and writes whole 128-byte (query, head) rows, eight per instruction.
   __syncthreads();  // every wavefront is done with the K/V tiles
   if (group) return true;
+  // (The thread number is made opaque here, so that this part's lane numbers and addresses are worked
+  // out again: held across the key loop they spilled two registers in the narrow index-driven kernels.)
+  int here = tid;
+  asm volatile("" : "+v"(here));
+  const int elane = here & 63, ec = here & 15, eG = elane >> 4;
   uint16_t* epi = smem + wave * (16 * kJ * kEpiStride);
 #pragma unroll
   for (int qb = 0; qb < kQB; ++qb) {
@@ -933,14 +983,14 @@ __device__ __forceinline__ bool attend(const AttnArgs& p, uint16_t* tiles, int b
       const float inv = 1.0f / l;
 #pragma unroll
       for (int dt = 0; dt < 4; ++dt) {
-        const int d0 = 16 * dt + 4 * G;
+        const int d0 = 16 * dt + 4 * eG;
         u32x2 o2;
         o2[0] = pack_bf16(w.O[qb][j][dt][0] * inv, w.O[qb][j][dt][1] * inv);
         o2[1] = pack_bf16(w.O[qb][j][dt][2] * inv, w.O[qb][j][dt][3] * inv);
-        *reinterpret_cast<u32x2*>(epi + (16 * j + c) * kEpiStride + d0) = o2;
+        *reinterpret_cast<u32x2*>(epi + (16 * j + ec) * kEpiStride + d0) = o2;
       }
-      if (p.lse && G == 0 && q0 + 16 * j + c < q_end)
-        p.lse[((int64_t)b * g.H + h) * g.NQ + q0 + 16 * j + c] =
+      if (p.lse && eG == 0 && q0 + 16 * j + ec < q_end)
+        p.lse[((int64_t)b * g.H + h) * g.NQ + q0 + 16 * j + ec] =
             ((kGen ? w.mref[qb][j] : 0.f) + log2f(l)) * kLn2;
     }
     // the wavefront's own writes, read back by other lanes of the same wavefront
@@ -949,12 +999,12 @@ __device__ __forceinline__ bool attend(const AttnArgs& p, uint16_t* tiles, int b
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront", "local");
 #pragma unroll
     for (int i = 0; i < 2 * kJ; ++i) {
-      const int row = i * 8 + (lane >> 3);
+      const int row = i * 8 + (elane >> 3);
       const int64_t q = q0 + row;
-      const u32x4 o4 = *reinterpret_cast<const u32x4*>(epi + row * kEpiStride + (lane & 7) * 8);
+      const u32x4 o4 = *reinterpret_cast<const u32x4*>(epi + row * kEpiStride + (elane & 7) * 8);
       if (q < q_end)
         *reinterpret_cast<u32x4*>(p.O + (((int64_t)b * g.NQ + q) * g.H + h) * kHeadDim +
-                                  (lane & 7) * 8) = o4;
+                                  (elane & 7) * 8) = o4;
     }
     __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront", "local");
     __builtin_amdgcn_wave_barrier();
