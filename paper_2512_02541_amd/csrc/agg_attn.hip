@@ -139,6 +139,22 @@ __device__ __forceinline__ float quad_max(float x) {
   return pair_max(x);
 }
 
+// LDS words through which wavefronts tell each other of rows that the fast path cannot handle: four
+// for the check inside the key loop, four for the one behind it.
+constexpr int kVoteWords = 2 * kWaves;
+
+// Whether x holds in any lane of the workgroup's first kWaves wavefronts (`mine`: this is one of them).
+// Passes one barrier.  (The library's workgroup-wide "or" passes three and reduces through LDS: a layer
+// of two frames of 16x16 14.55 us with it and 14.3 without, its block 43.5 / 43.1, index-driven, 40
+// frames, 2700 / 2684; longer calls alike.)
+__device__ __forceinline__ bool vote(bool x, uint32_t* words, int wave, int lane, bool mine) {
+  const bool any = __builtin_amdgcn_ballot_w64(x) != 0;
+  if (mine && lane == 0) words[wave] = any ? 1u : 0u;
+  __syncthreads();
+  const u32x4 all = *reinterpret_cast<const u32x4*>(words);
+  return __builtin_amdgcn_readfirstlane(all[0] | all[1] | all[2] | all[3]) != 0;
+}
+
 // zero-padded rows of the last tile: key index inside the tile >= valid -> -inf
 template <int kJ>
 __device__ __forceinline__ void mask_unit(f32x4 (&S)[2 * kJ], int kb, int valid, int G) {
@@ -597,8 +613,8 @@ __device__ __forceinline__ void tile_steps(Wave<kQB, kJ>& w, const u32x4* __rest
 // kSplit: the workgroup's other wavefronts walk other tiles, perhaps one fewer: no early check, whose
 // barriers would not match (the sums are looked at when the loops are done).
 template <int kSrc, bool kGen, bool kSplit, int kQB, int kJ, class FirstTile>
-__device__ __forceinline__ bool key_loop(Wave<kQB, kJ>& w, u32x4* __restrict__ lds, const KvSource& src,
-                                         int ntiles, int last_valid, int tid, int wave,
+__device__ __forceinline__ bool key_loop(Wave<kQB, kJ>& w, u32x4* __restrict__ lds, uint32_t* votes,
+                                         const KvSource& src, int ntiles, int last_valid, int tid, int wave,
                                          const FragAddr& fa, int G, FirstTile&& first_tile) {
   TileCopier<kSrc> copy;
   copy.init(src, lds, tid, wave);
@@ -641,7 +657,7 @@ __device__ __forceinline__ bool key_loop(Wave<kQB, kJ>& w, u32x4* __restrict__ l
       for (int qb = 0; qb < kQB; ++qb)
 #pragma unroll
         for (int j = 0; j < kJ; ++j) bad = bad || !(w.L[qb][j][0] < kSumHi);
-      if (__syncthreads_or(bad ? 1 : 0)) {
+      if (vote(bad, votes, wave, tid & 63, true)) {
         ok = false;
         break;
       }
@@ -676,7 +692,7 @@ constexpr int kTileLds = 2 * kLdsTiles * kTileElems;  // elements: K tiles, then
 // One workgroup's queries q_begin .. q_end - 1 (at most what four wavefronts hold) by one of the
 // two paths.  Returns false, without storing anything, when the fast path met a row it cannot
 // handle.
-// tiles: kTileLds elements of LDS per four wavefronts.
+// tiles: kTileLds elements of LDS per four wavefronts; votes: kVoteWords words.
 // kMode:
 //   kAlone      four wavefronts.
 //   kSplitKeys  (fast path) eight: the first four take the extras and the first half of the key
@@ -686,7 +702,7 @@ constexpr int kTileLds = 2 * kLdsTiles * kTileElems;  // elements: K tiles, then
 //   kTwin       eight: both groups do the same (so that their barriers match), the first stores.
 enum { kAlone, kSplitKeys, kTwin };
 template <int kSrc, bool kGen, int kQB, int kJ, int kMode = kAlone>
-__device__ __forceinline__ bool attend(const AttnArgs& p, uint16_t* tiles, int b, int h,
+__device__ __forceinline__ bool attend(const AttnArgs& p, uint16_t* tiles, uint32_t* votes, int b, int h,
                                        int64_t q_begin, int64_t q_end) {
   constexpr bool kSplit = kMode == kSplitKeys;
   static_assert(!(kGen && kSplit), "the general path's halves would need a common reference");
@@ -918,8 +934,8 @@ __device__ __forceinline__ bool attend(const AttnArgs& p, uint16_t* tiles, int b
     }
   };
 
-  const bool done = key_loop<kSrc, kGen, kSplit, kQB, kJ>(w, lds, src, ntiles, last_valid, tid, wave,
-                                                          fa, G, first_tile);
+  const bool done = key_loop<kSrc, kGen, kSplit, kQB, kJ>(w, lds, votes, src, ntiles, last_valid, tid,
+                                                          wave, fa, G, first_tile);
   if (kSplit) {
     // a loop passes one barrier per tile: the shorter one makes up for its missing tile
     if (ntiles < half) lds_barrier();
@@ -958,7 +974,7 @@ __device__ __forceinline__ bool attend(const AttnArgs& p, uint16_t* tiles, int b
     }
   if (!kGen) {
     if (!done) return false;  // uniform: decided by a workgroup-wide vote inside the loop
-    if (__syncthreads_or(unsafe ? 1 : 0)) return false;
+    if (vote(unsafe, votes + kWaves, wave, lane, group == 0)) return false;
   }
 
   // ---- normalise and store ----
@@ -966,7 +982,8 @@ __device__ __forceinline__ bool attend(const AttnArgs& p, uint16_t* tiles, int b
   // every instruction would scatter 8-byte pieces over 16 rows that lie 2*H*64 bytes apart.
   // Each wavefront instead turns its tile, a query block at a time, through a private part of the
   // (now idle) K/V LDS and writes whole 128-byte (query, head) rows, eight per instruction.
-  __syncthreads();  // every wavefront is done with the K/V tiles
+  // every wavefront is done with the K/V tiles (fast path: the vote's barrier has seen to that)
+  if (kGen) __syncthreads();
   if (group) return true;
   // (The thread number is made opaque here, so that this part's lane numbers and addresses are worked
   // out again: held across the key loop they spilled two registers in the narrow index-driven kernels.)
@@ -1112,13 +1129,14 @@ constexpr int tail_blocks(int tail_q) { return tail_q == 192 ? 3 : 2; }
 template <int kSrc, int kTailQ, bool kRedo>
 __global__ __launch_bounds__(kAttnThreads, kBlocksPerCu) void sga_attn_kernel(AttnArgs p) {
   __shared__ __align__(16) uint16_t tiles[kTileLds];
+  __shared__ __align__(16) uint32_t votes[kVoteWords];
   Work w;
   if (!workgroup_work(p, w)) return;
   bool done;
   if (kTailQ != 0 && w.tail)
-    done = attend<kSrc, false, tail_blocks(kTailQ), 1>(p, tiles, w.b, w.h, w.q_begin, w.q_end);
+    done = attend<kSrc, false, tail_blocks(kTailQ), 1>(p, tiles, votes, w.b, w.h, w.q_begin, w.q_end);
   else
-    done = attend<kSrc, false, 2, 2>(p, tiles, w.b, w.h, w.q_begin, w.q_end);
+    done = attend<kSrc, false, 2, 2>(p, tiles, votes, w.b, w.h, w.q_begin, w.q_end);
   if (done) return;
   if (!kRedo) {
     if (threadIdx.x == 0) *redo_slot(p, w) = kRedoMark;
@@ -1128,7 +1146,7 @@ __global__ __launch_bounds__(kAttnThreads, kBlocksPerCu) void sga_attn_kernel(At
 #pragma unroll 1
   for (int64_t q = w.q_begin; q < w.q_end; q += kWaves * wave_queries(2, 1)) {
     __syncthreads();  // the LDS is free
-    attend<kSrc, true, 2, 1>(again, tiles, w.b, w.h, q, min(w.q_end, q + kWaves * wave_queries(2, 1)));
+    attend<kSrc, true, 2, 1>(again, tiles, votes, w.b, w.h, q, min(w.q_end, q + kWaves * wave_queries(2, 1)));
   }
 }
 
@@ -1138,11 +1156,12 @@ __global__ __launch_bounds__(kAttnThreads, kBlocksPerCu) void sga_attn_kernel(At
 template <int kSrc>
 __global__ __launch_bounds__(2 * kAttnThreads, 2) void sga_attn_split_kernel(AttnArgs p) {
   __shared__ __align__(16) uint16_t tiles[2 * kTileLds];
+  __shared__ __align__(16) uint32_t votes[kVoteWords];
   Work w;
   if (!workgroup_work(p, w)) return;
-  if (attend<kSrc, false, 2, 1, kSplitKeys>(p, tiles, w.b, w.h, w.q_begin, w.q_end)) return;
+  if (attend<kSrc, false, 2, 1, kSplitKeys>(p, tiles, votes, w.b, w.h, w.q_begin, w.q_end)) return;
   __syncthreads();
-  attend<kSrc, true, 2, 1, kTwin>(p, tiles, w.b, w.h, w.q_begin, w.q_end);
+  attend<kSrc, true, 2, 1, kTwin>(p, tiles, votes, w.b, w.h, w.q_begin, w.q_end);
 }
 
 // The general path is a kernel of its own, launched behind the first on the same stream: it is
@@ -1155,14 +1174,15 @@ __global__ __launch_bounds__(2 * kAttnThreads, 2) void sga_attn_split_kernel(Att
 template <int kSrc, int kTailQ>
 __global__ __launch_bounds__(kAttnThreads, kBlocksPerCu) void sga_attn_general_kernel(AttnArgs p) {
   __shared__ __align__(16) uint16_t tiles[kTileLds];
+  __shared__ __align__(16) uint32_t votes[kVoteWords];
   Work w;
   if (!workgroup_work(p, w)) return;
   if (*redo_slot(p, w) != kRedoMark) return;  // same value in every lane
   __syncthreads();  // every wavefront has read the mark before any of them overwrites it
   if (kTailQ != 0 && w.tail)
-    attend<kSrc, true, tail_blocks(kTailQ), 1>(args_again(), tiles, w.b, w.h, w.q_begin, w.q_end);
+    attend<kSrc, true, tail_blocks(kTailQ), 1>(args_again(), tiles, votes, w.b, w.h, w.q_begin, w.q_end);
   else
-    attend<kSrc, true, 2, 2>(p, tiles, w.b, w.h, w.q_begin, w.q_end);
+    attend<kSrc, true, 2, 2>(p, tiles, votes, w.b, w.h, w.q_begin, w.q_end);
 }
 
 template <int kSrc, int kTailQ>
