@@ -369,6 +369,141 @@ __global__ __launch_bounds__(kGemmThreads, kEdge == 256 ? 2 : 4) void linear_ker
   }
 }
 
+// ---------------------------------------------------------------------------
+// The same layer for few tokens: 64 x 64 tiles, one per workgroup of eight wavefronts (16 tokens x 32
+// channels each), k 64 at a time through a ring of four steps of A and W.  With at most two tiles per
+// CU a launch is one chain of steps, and what counts is how little each of them waits: three steps are
+// under way, and a step's fragments are read while the one before is multiplied.  The tiles of a run of
+// channels follow each other, so that an XCD fetches an eighth of W instead of most of it.
+// Sums are in the order of linear_kernel: the same bits.
+//
+// Measured, Q/K/V + output projection, us, tiles of 128 / these: 261 rows of 1024 channels 13.5 + 13.3 /
+// 7.9 + 6.7; 522 rows 13.7 + 13.3 / 10.9 + 6.8; 522 rows of 512 channels 8.7 + 8.3 / 5.7 + 4.8.  At 522 rows the
+// output projection's launch and epilogue are 3.4 of 6.8, its copies alone 2.7 and its products, bound by LDS reads,
+// 2.6.  No faster: five or nine steps, fragments read in their own step (7.2), four wavefronts of
+// 32 x 32 (8.1), k shared between two groups of wavefronts (7.3), 32 x 64 or 128 x 64 tiles (7.2, 9.1); W read
+// straight into registers is twice as slow (13.8 and more).
+// ---------------------------------------------------------------------------
+constexpr int kFewEdge = 64;
+constexpr int kFewSteps = 4;                      // of the ring
+constexpr int kFewStepBytes = 2 * kFewEdge * kTK * 2;  // A's rows, then W's
+constexpr int kFewCopies = kFewStepBytes / 1024 / (kGemmThreads / 64);  // of a wavefront per step
+static_assert(kFewCopies == 2, "one eight-row copy of A and one of W per wavefront");
+
+// waits until the step `ahead` steps before the youngest one that was requested is in (ahead <= kMost)
+template <int kMost>
+__device__ __forceinline__ void wait_steps(int ahead) {
+  if (ahead >= kMost) wait_vm<kMost * kFewCopies>();
+  else if constexpr (kMost > 0) wait_steps<kMost - 1>(ahead);
+}
+
+template <bool kResidual>
+__global__ __launch_bounds__(kGemmThreads, 4) void linear_few_kernel(
+    const uint16_t* __restrict__ A, LinearOuts outs, const uint16_t* __restrict__ R, int64_t rows,
+    int N, int K, int gm, int gn) {
+  __shared__ __align__(16) char sm[kFewSteps * kFewStepBytes];
+  const int lane = threadIdx.x & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int c = lane & 15, G = lane >> 4;
+  const int wm = (wave & 3) * 16, wn = (wave >> 2) * 32;  // this wavefront's tokens and channels in the tile
+  const int nk = K / kTK;
+
+  // the tiles, all of one run of channels, then of the next; every XCD takes an equal run of that list
+  const int total = gm * gn * outs.count;  // (at most two per CU)
+  const int xcd = blockIdx.x % kGemmXcds;
+  const int at = total * xcd / kGemmXcds + (int)(blockIdx.x / kGemmXcds);
+  if (at >= total * (xcd + 1) / kGemmXcds) return;  // uniform for the workgroup, before any barrier
+  const int nt = at / gm;
+  const int64_t m0 = (int64_t)(at - nt * gm) * kFewEdge;
+  const int which = nt / gn, n0 = (nt - which * gn) * kFewEdge;
+
+  // Copies: wavefront w lands rows 8 w .. 8 w + 7 of A and of W (LDS layout and channel order as in
+  // linear_kernel: W's LDS row 16 ct + i of a wavefront's 32 channels is channel 2 i + ct).  Token rows
+  // past the end repeat the last one; never stored.
+  const uint32_t lds0 = (uint32_t)(uintptr_t)(lds_char*)sm + wave * 1024u;
+  const uint32_t lrow = lane >> 3, k2 = (uint32_t)K * 2;
+  const uint32_t chunk = ((lane & 7) ^ (lane >> 4) ^ (4 * (wave & 1))) * 16u;
+  const int64_t m = min(m0 + 8 * wave, rows - 1);
+  const uint16_t* abase = uniform_ptr(A + m * K);
+  const uint16_t* wbase = uniform_ptr(
+      outs.W[which] + (int64_t)(n0 + (wave >> 2) * 32 + (wave & 1) * 16 + ((wave >> 1) & 1)) * K);
+  const uint32_t aoff = __umul24((uint32_t)min((int64_t)lrow, rows - 1 - m), k2) + chunk;
+  const uint32_t woff = __umul24(lrow, 2 * k2) + chunk;
+  auto fetch = [&](int slot) {
+    dma16(abase, aoff, lds0 + slot * kFewStepBytes);
+    dma16(wbase, woff, lds0 + slot * kFewStepBytes + kFewStepBytes / 2);
+    abase += kTK;
+    wbase += kTK;
+  };
+
+  // what the epilogue adds, requested first: channels n, n + 1 of tokens mw .. mw + 3
+  const float* __restrict__ bias = outs.bias[which];
+  const int n = n0 + wn + 2 * c;
+  const int64_t mw = m0 + wm + 4 * G;
+  const float b0 = bias ? bias[n] : 0.f, b1 = bias ? bias[n + 1] : 0.f;
+  uint32_t rr[4] = {0u, 0u, 0u, 0u};
+  if (kResidual) {
+#pragma unroll
+    for (int r = 0; r < 4; ++r)
+      if (mw + r < rows) rr[r] = *reinterpret_cast<const uint32_t*>(R + (mw + r) * N + n);
+  }
+
+#pragma unroll
+  for (int s = 0; s < kFewSteps - 1; ++s)
+    if (s < nk) fetch(s);
+  f32x4 acc[2] = {f32x4{0.f, 0.f, 0.f, 0.f}, f32x4{0.f, 0.f, 0.f, 0.f}};
+  struct Step { Frag a[2], w[2][2]; };  // [half of k], [channel tile]
+  const int f0 = c * 128 + ((G ^ ((c >> 1) & 7)) * 16);
+  auto read = [&](Step& f, int slot) {
+    const lds_char* s = (const lds_char*)sm + slot * kFewStepBytes;
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+      const int fh = f0 ^ (64 * h);
+#pragma unroll
+      for (int a = 0; a < 2; ++a)
+        f.w[h][a].u = *reinterpret_cast<const __attribute__((address_space(3))) u32x4*>(
+            s + kFewStepBytes / 2 + (wn + 16 * a) * 128 + fh);
+      f.a[h].u = *reinterpret_cast<const __attribute__((address_space(3))) u32x4*>(s + wm * 128 + fh);
+    }
+  };
+  int slot = 0;  // of the step whose fragments were read last
+  wait_steps<kFewSteps - 2>(nk - 1);
+  lds_barrier();
+  Step even, odd;
+  read(even, 0);
+  auto step = [&](int k, const Step& now, Step& then) {
+    if (k + 1 < nk) {
+      wait_steps<kFewSteps - 3>(nk - 2 - k);
+      lds_barrier();  // everybody's copies of step k + 1 are in, and the slot of step k - 1 is free
+      if (k + kFewSteps - 1 < nk) fetch((slot + kFewSteps - 1) % kFewSteps);
+      slot = (slot + 1) % kFewSteps;
+      read(then, slot);
+    }
+#pragma unroll
+    for (int h = 0; h < 2; ++h)
+#pragma unroll
+      for (int a = 0; a < 2; ++a)
+        acc[a] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(now.a[h].h, now.w[h][a].h, acc[a], 0, 0, 0);
+  };
+  for (int k = 0;; ++k) {
+    step(k, even, odd);
+    if (++k >= nk) break;
+    step(k, odd, even);
+    if (k + 1 >= nk) break;
+  }
+
+#pragma unroll
+  for (int r = 0; r < 4; ++r)
+    if (mw + r < rows) {
+      float lo = acc[0][r] + b0, hi = acc[1][r] + b1;
+      if (kResidual) {
+        lo += lo16(rr[r]);
+        hi += hi16(rr[r]);
+      }
+      *reinterpret_cast<uint32_t*>(outs.Y[which] + (mw + r) * N + n) = pack2(lo, hi);
+    }
+}
+
 hipError_t launch_layernorm(const void* x, const float* gamma, const float* beta, void* y,
                             int64_t rows, int C, float eps, hipStream_t st) {
   if (C % 8 != 0 || C > 64 * 8 * kLnMaxChunks) return hipErrorInvalidValue;
@@ -403,6 +538,17 @@ static hipError_t launch_linear_tiles(const uint16_t* A, const LinearOuts& outs,
   return hipGetLastError();
 }
 
+static hipError_t launch_linear_few(const uint16_t* A, const LinearOuts& outs, const uint16_t* R,
+                                    int64_t rows, int N, int K, int tiles, hipStream_t st) {
+  const int gm = (int)((rows + kFewEdge - 1) / kFewEdge), gn = N / kFewEdge;
+  const dim3 grid((unsigned)((tiles + kGemmXcds - 1) / kGemmXcds * kGemmXcds));
+  if (R)
+    hipLaunchKernelGGL(linear_few_kernel<true>, grid, dim3(kGemmThreads), 0, st, A, outs, R, rows, N, K, gm, gn);
+  else
+    hipLaunchKernelGGL(linear_few_kernel<false>, grid, dim3(kGemmThreads), 0, st, A, outs, R, rows, N, K, gm, gn);
+  return hipGetLastError();
+}
+
 // Times of a launch in microseconds, from what a round of tiles took at K = 1024: 256-wide tiles 33,
 // one to a CU; 128-wide ones 20.6 two to a CU and 14 alone, 7 where a CU's last one runs alone behind
 // others.  They are taken to follow K, which stores and starts do not; at K = 128 to 4096 and 261 to
@@ -421,10 +567,17 @@ hipError_t launch_linear(const void* A, const LinearOuts& outs, const void* R, i
                          int K, hipStream_t st) {
   if (K % 64 != 0 || N % 64 != 0 || outs.count < 1 || outs.count > 3) return hipErrorInvalidValue;
   (void)hipGetLastError();
+  const uint16_t* a = (const uint16_t*)A;
+  const uint16_t* r = (const uint16_t*)R;
+  // Up to two 64-wide tiles per CU.  Tiles of 128 / of 64, us, by the number of the latter at C = 1024: 144
+  // 13.3 / 6.8; 288 13.3 / 9.7; 352 13.2 / 10.2; 432 13.7 / 10.9; beyond the line 688 14.1 / 16.7; 864 14.8 / 17.8.
+  // C = 1280: 260 15.5 / 10.8; 780 17.0 / 20.7.  C = 512: 216 8.7 / 5.7; 344 8.8 / 7.7; 1032 12.9 / 14.9.
+  const int64_t few = (rows + kFewEdge - 1) / kFewEdge * (N / kFewEdge) * outs.count;
+  if (few <= 2 * kGemmCus) return launch_linear_few(a, outs, r, rows, N, K, (int)few, st);
   // Large tiles move half the bytes per product, small ones fill the chip and its last round: the
   // rows of whole rounds of large tiles go to them and the others to small tiles, if that is at
   // least 6 % ahead of large tiles alone (a second launch costs 4 us).  Measured for the Q/K/V and
-  // the output projection at C = 1024, large / small / chosen, us: 522 rows 30 + 29 / 15 + 13 / 14 + 14;
+  // the output projection at C = 1024, large / small / chosen, us:
   // 5 496 rows 58 + 32 / 46 + 20 / 45 + 21; 10 992 rows 90 + 35 / 85 + 32 / 82 + 31; 32 976 rows
   // 232 + 110 / 270 + 104 / 229 + 105; 137 400 rows 817 + 325 / 1022 + 374 / large.
   const int64_t per_m = (int64_t)((N + 255) / 256) * outs.count;
@@ -436,8 +589,6 @@ hipError_t launch_linear(const void* A, const LinearOuts& outs, const void* R, i
   const double both = split ? linear_time(split, 256, N, K, outs.count) +
                                   linear_time(rows - split, 128, N, K, outs.count) + 4.0
                             : large;
-  const uint16_t* a = (const uint16_t*)A;
-  const uint16_t* r = (const uint16_t*)R;
   if (small < 0.97 * large && small <= both) return launch_linear_tiles<128>(a, outs, r, rows, N, K, st);
   if (both >= 0.94 * large) return launch_linear_tiles<256>(a, outs, r, rows, N, K, st);
   const hipError_t e = launch_linear_tiles<256>(a, outs, r, split, N, K, st);

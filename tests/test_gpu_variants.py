@@ -114,6 +114,21 @@ def test_projection_tiles(H, rows):
     assert float(err.max()) <= 6e-2 and float(err.mean()) <= 4e-3, (float(err.max()), float(err.mean()))
 
 
+# (heads, rows) of few tiles of 64 (linear_few_kernel), and of the smallest that take tiles of 128
+FEW_PROJECTIONS = [
+    (1, 63), (2, 66), (3, 192), (4, 195), (5, 66),  # one to five k steps (the ring has four) around whole tiles
+    (16, 639), (16, 642),  # the most token tiles of the Q, K and V projections, and one more
+    (33, 192),             # 33 k steps
+    (3, 9999),             # tiles of 128: the last of every matrix half empty
+]
+
+
+@pytest.mark.parametrize("H,rows", FEW_PROJECTIONS)
+def test_projection_few_tokens(H, rows):
+    """The same check around the sizes at which a projection changes from tiles of 64 to larger ones."""
+    test_projection_tiles(H, rows)
+
+
 @pytest.mark.parametrize("H", [1, 3, 16, 33])
 @pytest.mark.parametrize("B,nq", [(1, 1024), (2, 1026), (1, 70000)])
 def test_mean_split_by_heads(H, B, nq):
