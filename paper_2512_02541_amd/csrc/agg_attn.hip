@@ -501,6 +501,10 @@ __device__ __forceinline__ void tile_steps(Wave<kQB, kJ>& w, const u32x4* __rest
                                            int valid, const FragAddr& fa, int G) {
 #pragma unroll
   for (int sg = 0; sg < 2 * kQB; ++sg) {
+    // A last tile of up to 32 keys: its second block is padding throughout.  (Left out from here on; a
+    // separate body for such tiles spilled 80 registers.  Per-frame attention over 1374 keys, 90 frames, 663 /
+    // 651 us; layer of 2 frames of 16x16 14.3 / 14.0; 9.5 ms calls alike.)
+    if (kLast && sg == kQB && valid <= kTileRows / 2) break;
     const int kb = sg / kQB, qb = sg % kQB;
     const int un = sg + kQB - 1;              // unit whose scores start now
     const int tq = un % kQB;                  // its query block

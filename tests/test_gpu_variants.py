@@ -194,6 +194,23 @@ def test_key_counts_of_four_wavefront_kernels(nkeys):
     _frame_case(33, nkeys, 8, 9400 + nkeys)
 
 
+@pytest.mark.parametrize("nkeys", [31, 32, 33, 96, 97, 1568, 1569])
+def test_half_filled_last_tiles(nkeys):
+    """A last tile of up to 32 keys is walked half: 31, 32 and 33 keys in it, as the only tile, the second
+    and the 25th, at each width, in the launches whose wavefronts share the keys, and redone."""
+    for width, nq in QUERIES_BY_WIDTH.items():
+        shape = _shape_of_keys(1, nq, nkeys, 16)
+        q, k, v = inputs.iid_qkv(1, nq, 16, 64, seed=9700 + nkeys + width, device="cuda")
+        run_case(shape, q, k, v, rows=_some_rows(nq), what="%d keys, width %d" % (nkeys, width))
+        _idx_case(shape, q, k, v, "%d keys, width %d" % (nkeys, width))
+    shape = _shape_of_keys(1, nkeys + 70, nkeys, 2)
+    q, k, v = inputs.iid_qkv(1, shape.NQ, 2, 64, seed=9800 + nkeys, device="cuda")
+    run_case(shape, q, k, v, what="%d shared keys" % nkeys)
+    _idx_case(shape, q, k, v, "%d shared keys" % nkeys)
+    _frame_case(33, nkeys, 8, 9900 + nkeys)
+    _frame_case(33, nkeys, 8, 9900 + nkeys, _spoil("own"))
+
+
 def _frame_case(N, L, H, seed, spoil=None):
     shape = agg.make_shape(1, N, 1, L, 0, H, 64, 1, 1, 0, flags=0)
     q, k, v = inputs.iid_qkv(1, shape.NQ, H, 64, seed=seed, device="cuda")
