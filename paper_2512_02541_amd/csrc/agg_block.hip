@@ -538,6 +538,9 @@ static hipError_t launch_linear_tiles(const uint16_t* A, const LinearOuts& outs,
   return hipGetLastError();
 }
 
+static int64_t few_tiles(int64_t rows, int N, int count) {
+  return (rows + kFewEdge - 1) / kFewEdge * (N / kFewEdge) * count;
+}
 static hipError_t launch_linear_few(const uint16_t* A, const LinearOuts& outs, const uint16_t* R,
                                     int64_t rows, int N, int K, int tiles, hipStream_t st) {
   const int gm = (int)((rows + kFewEdge - 1) / kFewEdge), gn = N / kFewEdge;
@@ -572,11 +575,11 @@ hipError_t launch_linear(const void* A, const LinearOuts& outs, const void* R, i
   // Up to two 64-wide tiles per CU.  Tiles of 128 / of 64, us, by the number of the latter at C = 1024: 144
   // 13.3 / 6.8; 288 13.3 / 9.7; 352 13.2 / 10.2; 432 13.7 / 10.9; beyond the line 688 14.1 / 16.7; 864 14.8 / 17.8.
   // C = 1280: 260 15.5 / 10.8; 780 17.0 / 20.7.  C = 512: 216 8.7 / 5.7; 344 8.8 / 7.7; 1032 12.9 / 14.9.
-  const int64_t few = (rows + kFewEdge - 1) / kFewEdge * (N / kFewEdge) * outs.count;
+  const int64_t few = few_tiles(rows, N, outs.count);
   if (few <= 2 * kGemmCus) return launch_linear_few(a, outs, r, rows, N, K, (int)few, st);
   // Large tiles move half the bytes per product, small ones fill the chip and its last round: the
   // rows of whole rounds of large tiles go to them and the others to small tiles, if that is at
-  // least 6 % ahead of large tiles alone (a second launch costs 4 us).  Measured for the Q/K/V and
+  // least 6 % ahead of large tiles alone and 3 % of small ones (a second launch costs 4 us).  Measured for the Q/K/V and
   // the output projection at C = 1024, large / small / chosen, us:
   // 5 496 rows 58 + 32 / 46 + 20 / 45 + 21; 10 992 rows 90 + 35 / 85 + 32 / 82 + 31; 32 976 rows
   // 232 + 110 / 270 + 104 / 229 + 105; 137 400 rows 817 + 325 / 1022 + 374 / large.
@@ -586,16 +589,25 @@ hipError_t launch_linear(const void* A, const LinearOuts& outs, const void* R, i
   const int64_t split = whole * 256 < rows ? whole * 256 : 0;
   const double large = linear_time(rows, 256, N, K, outs.count);
   const double small = linear_time(rows, 128, N, K, outs.count);
-  const double both = split ? linear_time(split, 256, N, K, outs.count) +
-                                  linear_time(rows - split, 128, N, K, outs.count) + 4.0
-                            : large;
-  if (small < 0.97 * large && small <= both) return launch_linear_tiles<128>(a, outs, r, rows, N, K, st);
+  // The others take tiles of 64 where these are few enough: 7.5 us up to one per CU, 11 up to two, where a
+  // single round of small tiles takes 14 to 20.  Whole block, others in small tiles / in tiles of 64 (and
+  // then also where that makes two launches the better choice): 16 frames of 37x37, 239 others, 731.5 /
+  // 722.3; per-frame, 8 frames 188.5 / 181.3; 96 frames, 832, 1879 / 1864; 42 frames of 28x37 622 / 607;
+  // 167 frames of 16x16, 12 heads, 364 / 353.
+  const int64_t few_rest = few_tiles(rows - split, N, outs.count);
+  const double rest_time = few_rest > 2 * kGemmCus ? linear_time(rows - split, 128, N, K, outs.count)
+                                                   : K / 1024.0 * (few_rest > kGemmCus ? 11.0 : 7.5);
+  const double both = split ? linear_time(split, 256, N, K, outs.count) + rest_time + 4.0 : large;
+  if (small < 0.97 * large && small <= 1.03 * both) return launch_linear_tiles<128>(a, outs, r, rows, N, K, st);
   if (both >= 0.94 * large) return launch_linear_tiles<256>(a, outs, r, rows, N, K, st);
   const hipError_t e = launch_linear_tiles<256>(a, outs, r, split, N, K, st);
   if (e != hipSuccess) return e;
   LinearOuts rest = outs;
   for (int i = 0; i < outs.count; ++i) rest.Y[i] += split * N;
-  return launch_linear_tiles<128>(a + split * K, rest, r ? r + split * N : nullptr, rows - split, N, K, st);
+  a += split * K;
+  if (r) r += split * N;
+  if (few_rest <= 2 * kGemmCus) return launch_linear_few(a, rest, r, rows - split, N, K, (int)few_rest, st);
+  return launch_linear_tiles<128>(a, rest, r, rows - split, N, K, st);
 }
 
 }  // namespace agg

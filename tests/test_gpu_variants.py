@@ -84,7 +84,8 @@ PROJECTIONS = [
     (3, 999),           # 192 channels: the last small tile of every matrix is half empty
     (4, 66048),         # large tiles, several per workgroup, all whole
     (5, 261),           # 320 channels
-    (16, 21999),        # whole rounds of large tiles, the other rows in small ones
+    (16, 21999),        # whole rounds of large tiles, the other rows in tiles of 64 (Q/K/V) and of 128
+    (16, 34353),        # large tiles alone (Q/K/V); ... and others in tiles of 64 with the residual
     (33, 30000),        # 2112 channels: the last large tile of every matrix is a quarter full
 ]
 
