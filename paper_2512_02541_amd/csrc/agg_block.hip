@@ -5,6 +5,7 @@
 // follow the MFMA conventions of the attention kernel.
 #include "agg_internal.h"
 #include "agg_lds_copy.h"
+#include "agg_linear_plan.h"
 
 namespace agg {
 
@@ -136,8 +137,6 @@ __global__ __launch_bounds__(kLnThreads) void layernorm_kernel(const uint16_t* _
 // ---------------------------------------------------------------------------
 constexpr int kGemmThreads = 512;
 constexpr int kTK = 64;
-constexpr int kGemmXcds = 8;
-constexpr int kGemmCus = 256;
 constexpr int kSlots = 5;
 
 // kEdge: 256 or 128, the tile's tokens and channels
@@ -384,7 +383,6 @@ __global__ __launch_bounds__(kGemmThreads, kEdge == 256 ? 2 : 4) void linear_ker
 // 32 x 32 (8.1), k shared between two groups of wavefronts (7.3), 32 x 64 or 128 x 64 tiles (7.2, 9.1); W read
 // straight into registers is twice as slow (13.8 and more).
 // ---------------------------------------------------------------------------
-constexpr int kFewEdge = 64;
 constexpr int kFewSteps = 4;                      // of the ring
 constexpr int kFewStepBytes = 2 * kFewEdge * kTK * 2;  // A's rows, then W's
 constexpr int kFewCopies = kFewStepBytes / 1024 / (kGemmThreads / 64);  // of a wavefront per step
@@ -538,12 +536,10 @@ static hipError_t launch_linear_tiles(const uint16_t* A, const LinearOuts& outs,
   return hipGetLastError();
 }
 
-static int64_t few_tiles(int64_t rows, int N, int count) {
-  return (rows + kFewEdge - 1) / kFewEdge * (N / kFewEdge) * count;
-}
 static hipError_t launch_linear_few(const uint16_t* A, const LinearOuts& outs, const uint16_t* R,
-                                    int64_t rows, int N, int K, int tiles, hipStream_t st) {
+                                    int64_t rows, int N, int K, hipStream_t st) {
   const int gm = (int)((rows + kFewEdge - 1) / kFewEdge), gn = N / kFewEdge;
+  const int tiles = (int)few_tiles(rows, N, outs.count);
   const dim3 grid((unsigned)((tiles + kGemmXcds - 1) / kGemmXcds * kGemmXcds));
   if (R)
     hipLaunchKernelGGL(linear_few_kernel<true>, grid, dim3(kGemmThreads), 0, st, A, outs, R, rows, N, K, gm, gn);
@@ -552,18 +548,11 @@ static hipError_t launch_linear_few(const uint16_t* A, const LinearOuts& outs, c
   return hipGetLastError();
 }
 
-// Times of a launch in microseconds, from what a round of tiles took at K = 1024: 256-wide tiles 33,
-// one to a CU; 128-wide ones 20.6 two to a CU and 14 alone, 7 where a CU's last one runs alone behind
-// others.  They are taken to follow K, which stores and starts do not; at K = 128 to 4096 and 261 to
-// 137 400 rows (184 launches) the choice below took 0.85 to 1.03 of the better single size, once 1.07
-// (K = 512, 21 984 rows, three matrices: 46.3 against 43.4 us with small tiles alone).
-static double linear_time(int64_t rows, int edge, int N, int K, int count) {
-  const int64_t tiles = (rows + edge - 1) / edge * ((N + edge - 1) / edge) * count;
-  const int64_t mine = (tiles + kGemmXcds - 1) / kGemmXcds;  // of one XCD, which has 32 CUs
-  const double k = K / 1024.0;
-  if (edge == 256) return k * 33.0 * ((mine + 31) / 32);
-  const int64_t full = mine / 64, rest = mine % 64;
-  return k * (20.6 * full + (rest == 0 ? 0.0 : rest > 32 ? 20.6 : full ? 7.0 : 14.0));
+static hipError_t launch_linear_edge(int edge, const uint16_t* A, const LinearOuts& outs, const uint16_t* R,
+                                     int64_t rows, int N, int K, hipStream_t st) {
+  if (edge == kFewEdge) return launch_linear_few(A, outs, R, rows, N, K, st);
+  if (edge == kSmallEdge) return launch_linear_tiles<kSmallEdge>(A, outs, R, rows, N, K, st);
+  return launch_linear_tiles<kLargeEdge>(A, outs, R, rows, N, K, st);
 }
 
 hipError_t launch_linear(const void* A, const LinearOuts& outs, const void* R, int64_t rows, int N,
@@ -572,42 +561,14 @@ hipError_t launch_linear(const void* A, const LinearOuts& outs, const void* R, i
   (void)hipGetLastError();
   const uint16_t* a = (const uint16_t*)A;
   const uint16_t* r = (const uint16_t*)R;
-  // Up to two 64-wide tiles per CU.  Tiles of 128 / of 64, us, by the number of the latter at C = 1024: 144
-  // 13.3 / 6.8; 288 13.3 / 9.7; 352 13.2 / 10.2; 432 13.7 / 10.9; beyond the line 688 14.1 / 16.7; 864 14.8 / 17.8.
-  // C = 1280: 260 15.5 / 10.8; 780 17.0 / 20.7.  C = 512: 216 8.7 / 5.7; 344 8.8 / 7.7; 1032 12.9 / 14.9.
-  const int64_t few = few_tiles(rows, N, outs.count);
-  if (few <= 2 * kGemmCus) return launch_linear_few(a, outs, r, rows, N, K, (int)few, st);
-  // Large tiles move half the bytes per product, small ones fill the chip and its last round: the
-  // rows of whole rounds of large tiles go to them and the others to small tiles, if that is at
-  // least 6 % ahead of large tiles alone and 3 % of small ones (a second launch costs 4 us).  Measured for the Q/K/V and
-  // the output projection at C = 1024, large / small / chosen, us:
-  // 5 496 rows 58 + 32 / 46 + 20 / 45 + 21; 10 992 rows 90 + 35 / 85 + 32 / 82 + 31; 32 976 rows
-  // 232 + 110 / 270 + 104 / 229 + 105; 137 400 rows 817 + 325 / 1022 + 374 / large.
-  const int64_t per_m = (int64_t)((N + 255) / 256) * outs.count;
-  const int64_t gm = (rows + 255) / 256;
-  const int64_t whole = gm * per_m / kGemmCus * kGemmCus / per_m;  // token tiles that fill whole rounds
-  const int64_t split = whole * 256 < rows ? whole * 256 : 0;
-  const double large = linear_time(rows, 256, N, K, outs.count);
-  const double small = linear_time(rows, 128, N, K, outs.count);
-  // The others take tiles of 64 where these are few enough: 7.5 us up to one per CU, 11 up to two, where a
-  // single round of small tiles takes 14 to 20.  Whole block, others in small tiles / in tiles of 64 (and
-  // then also where that makes two launches the better choice): 16 frames of 37x37, 239 others, 731.5 /
-  // 722.3; per-frame, 8 frames 188.5 / 181.3; 96 frames, 832, 1879 / 1864; 42 frames of 28x37 622 / 607;
-  // 167 frames of 16x16, 12 heads, 364 / 353.
-  const int64_t few_rest = few_tiles(rows - split, N, outs.count);
-  const double rest_time = few_rest > 2 * kGemmCus ? linear_time(rows - split, 128, N, K, outs.count)
-                                                   : K / 1024.0 * (few_rest > kGemmCus ? 11.0 : 7.5);
-  const double both = split ? linear_time(split, 256, N, K, outs.count) + rest_time + 4.0 : large;
-  if (small < 0.97 * large && small <= 1.03 * both) return launch_linear_tiles<128>(a, outs, r, rows, N, K, st);
-  if (both >= 0.94 * large) return launch_linear_tiles<256>(a, outs, r, rows, N, K, st);
-  const hipError_t e = launch_linear_tiles<256>(a, outs, r, split, N, K, st);
+  const LinearPlan plan = plan_linear(rows, N, K, outs.count);
+  if (plan.split == 0) return launch_linear_edge(plan.edge, a, outs, r, rows, N, K, st);
+  const hipError_t e = launch_linear_edge(kLargeEdge, a, outs, r, plan.split, N, K, st);
   if (e != hipSuccess) return e;
   LinearOuts rest = outs;
-  for (int i = 0; i < outs.count; ++i) rest.Y[i] += split * N;
-  a += split * K;
-  if (r) r += split * N;
-  if (few_rest <= 2 * kGemmCus) return launch_linear_few(a, rest, r, rows - split, N, K, (int)few_rest, st);
-  return launch_linear_tiles<128>(a, rest, r, rows - split, N, K, st);
+  for (int i = 0; i < outs.count; ++i) rest.Y[i] += plan.split * N;
+  return launch_linear_edge(plan.edge, a + plan.split * K, rest, r ? r + plan.split * N : nullptr,
+                            rows - plan.split, N, K, st);
 }
 
 }  // namespace agg

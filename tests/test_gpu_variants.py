@@ -77,17 +77,25 @@ def _bf16(t):
     return t.to(torch.bfloat16).double()
 
 
-# (heads, rows): which tiles a projection takes depends on both (launch_linear)
-PROJECTIONS = [
-    (1, 3), (1, 129),   # one k step, one and two small tiles of tokens
-    (1, 30000),         # one k step and several small tiles per workgroup
-    (3, 999),           # 192 channels: the last small tile of every matrix is half empty
-    (4, 66048),         # large tiles, several per workgroup, all whole
-    (5, 261),           # 320 channels
-    (16, 21999),        # whole rounds of large tiles, the other rows in tiles of 64 (Q/K/V) and of 128
-    (16, 34353),        # large tiles alone (Q/K/V); ... and others in tiles of 64 with the residual
-    (33, 30000),        # 2112 channels: the last large tile of every matrix is a quarter full
-]
+# (heads, rows) -> the tiles of the Q, K and V projections and of the output projection, the one with the
+# residual (plan_linear; test_launch_plan.py checks them without a GPU).  "256+64": the rows of whole rounds
+# in tiles of 256, the others in tiles of 64, in a launch of their own.
+PROJECTIONS = {
+    (1, 3): ("64", "64"), (1, 129): ("64", "64"),
+    (1, 30000): ("128", "64"),
+    (3, 999): ("64", "64"),
+    (4, 66048): ("256+64", "128"),      # every tile of 128 and 256 whole
+    (5, 261): ("64", "64"),
+    (16, 21999): ("256+64", "256+128"),
+    (16, 34353): ("256", "256+64"),
+    (33, 30000): ("256", "256+128"),    # 2112 channels: the last large tile of every matrix is a quarter full
+    (1, 33000): ("128", "128"),         # one k step, at most one tile per workgroup with the residual
+    (1, 99999): ("128", "128"),         # ... and several
+    (2, 69999): ("128", "128"),         # two k steps, several tiles per workgroup
+    (3, 12000): ("128", "128"),         # 192 channels: the last tile of every matrix is half empty
+    (3, 49998): ("256", "256"),         # three k steps, and a quarter of every large tile empty
+    (5, 45000): ("128", "128"),         # 320 channels, several tiles per workgroup
+}
 
 
 @pytest.mark.parametrize("H,rows", PROJECTIONS)
@@ -115,13 +123,15 @@ def test_projection_tiles(H, rows):
     assert float(err.max()) <= 6e-2 and float(err.mean()) <= 4e-3, (float(err.max()), float(err.mean()))
 
 
-# (heads, rows) of few tiles of 64 (linear_few_kernel), and of the smallest that take tiles of 128
-FEW_PROJECTIONS = [
-    (1, 63), (2, 66), (3, 192), (4, 195), (5, 66),  # one to five k steps (the ring has four) around whole tiles
-    (16, 639), (16, 642),  # the most token tiles of the Q, K and V projections, and one more
-    (33, 192),             # 33 k steps
-    (3, 9999),             # tiles of 128: the last of every matrix half empty
-]
+# The same around the sizes at which a projection changes from tiles of 64 to larger ones
+FEW_PROJECTIONS = {
+    # one to five k steps (the ring has four) around whole tiles
+    (1, 63): ("64", "64"), (2, 66): ("64", "64"), (3, 192): ("64", "64"), (4, 195): ("64", "64"), (5, 66): ("64", "64"),
+    (16, 639): ("64", "64"), (16, 642): ("128", "64"),  # the most token tiles of Q, K and V, and one more
+    (33, 192): ("64", "64"),    # 33 k steps
+    (3, 9999): ("128", "64"),   # tiles of 128: the last of every matrix half empty
+    (2, 16383): ("128", "64"), (2, 16386): ("128", "128"),  # the most token tiles of the output, and one more
+}
 
 
 @pytest.mark.parametrize("H,rows", FEW_PROJECTIONS)

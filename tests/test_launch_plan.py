@@ -1,8 +1,9 @@
-"""The attention's launch plan, without a GPU: the plan is plain host code, compiled here by itself.
+"""The launch plans of the attention and of the projections, without a GPU: they are plain host code,
+compiled here by themselves.
 
-Which kernel a call runs follows from its queries, pairs and key tiles alone.  The GPU tests name the
-kernels and widths they are for; this file checks that their sizes still lead there, so that a
-changed rule cannot quietly leave a kernel without its tests."""
+Which kernel a call runs follows from its queries, pairs and key tiles alone, or from a projection's rows,
+channels and number of matrices.  The GPU tests name the kernels and widths they are for; this file checks
+that their sizes still lead there, so that a changed rule cannot quietly leave a kernel without its tests."""
 import os
 import subprocess
 
@@ -26,14 +27,32 @@ int main() {
 """
 
 
-@pytest.fixture(scope="module")
-def plan(tmp_path_factory):
-    """(queries, pairs, keys) -> (kernel width of the last workgroups or "split", redone in place)"""
-    d = tmp_path_factory.mktemp("plan")
-    (d / "plan.cpp").write_text(DRIVER)
+LINEAR_DRIVER = r"""
+#include <stdio.h>
+#include "agg_linear_plan.h"
+int main() {
+  long long rows;
+  int channels, count;
+  while (scanf("%lld %d %d", &rows, &channels, &count) == 3) {
+    const agg::LinearPlan p = agg::plan_linear(rows, channels, channels, count);
+    printf("%lld %d\n", (long long)p.split, p.edge);
+  }
+}
+"""
+
+
+def _compile(d, text):
+    (d / "plan.cpp").write_text(text)
     exe = str(d / "plan")
     subprocess.check_call(["g++", "-std=c++17", "-O1", "-Wall", "-Werror", "-Wno-unused-function", "-I", b.CSRC,
                            "-o", exe, str(d / "plan.cpp")])
+    return exe
+
+
+@pytest.fixture(scope="module")
+def plan(tmp_path_factory):
+    """(queries, pairs, keys) -> (kernel width of the last workgroups or "split", redone in place)"""
+    exe = _compile(tmp_path_factory.mktemp("plan"), DRIVER)
 
     def ask(nq, npairs, nkeys):
         text = "%d %d %d\n" % (nq, npairs, -(-nkeys // 64))
@@ -91,3 +110,55 @@ def test_tail_cases_reach_their_kernels(plan):
     want = ["split", 192, 192, 192, 192, 192, 192, 0, 192]
     assert [plan(nq, B * H, -(-nq // s))[0] for B, nq, H, s in variants.TAILS] == want
     assert [plan(L, 256, L)[0] for L in (449, 600, 700, 769)] == [0, 128, 192, 128]
+
+
+@pytest.fixture(scope="module")
+def tiles(tmp_path_factory):
+    """[(rows, channels, matrices)] -> [(rows in the first of two launches or 0, edge of the others' tiles)]"""
+    exe = _compile(tmp_path_factory.mktemp("linear"), LINEAR_DRIVER)
+
+    def ask(sizes):
+        text = "".join("%d %d %d\n" % s for s in sizes)
+        out = subprocess.run([exe], input=text, text=True, check=True, stdout=subprocess.PIPE).stdout
+        got = [tuple(int(x) for x in line.split()) for line in out.splitlines()]
+        assert len(got) == len(sizes)
+        return got
+
+    return ask
+
+
+def _route(split, edge):
+    return "256+%d" % edge if split else "%d" % edge
+
+
+def test_every_row_has_a_tile(tiles):
+    sizes = [(rows, 64 * heads, count) for heads in (1, 2, 3, 4, 5, 8, 16, 20, 33, 40, 64) for count in (1, 3)
+             for rows in (1, 63, 64, 65, 255, 256, 257, 5496, 10922, 21984, 43521, 65536, 137400, 457542, 1099200)]
+    for (rows, channels, count), (split, edge) in zip(sizes, tiles(sizes)):
+        assert edge in (64, 128, 256) and 0 <= split < rows and split % 256 == 0
+        assert edge != 256 or split == 0
+        # tiles of 64: at most two per CU
+        few = -(-(rows - split) // 64) * (channels // 64) * count
+        assert edge != 64 or few <= 512
+        # the rows in a launch of their own fill whole rounds of one large tile per CU, but for less than a token tile
+        large = split // 256 * (-(-channels // 256)) * count
+        assert split == 0 or large > 0 and -large % 256 < -(-channels // 256) * count
+
+
+def test_projection_cases_reach_their_kernels(tiles):
+    seen = set()
+    for cases in (variants.PROJECTIONS, variants.FEW_PROJECTIONS):
+        for (heads, rows), want in cases.items():
+            got = tiles([(rows, 64 * heads, 3), (rows, 64 * heads, 1)])
+            assert tuple(_route(*g) for g in got) == want, (heads, rows, got)
+            for residual, (split, edge) in enumerate(got):
+                seen.add((edge, residual, heads))
+                if split:
+                    seen |= {(256, residual, heads), ("behind 256", edge, residual)}
+    # with and without the residual: one to five k steps in tiles of 64; one, two, three and five in tiles of
+    # 128; three, the fewest that take tiles of 256
+    for residual in (0, 1):
+        for steps in (1, 2, 3, 5):
+            assert (64, residual, steps) in seen and (128, residual, steps) in seen
+        assert (64, residual, 4) in seen and (256, residual, 3) in seen
+    assert {("behind 256", 64, 0), ("behind 256", 64, 1), ("behind 256", 128, 1)} <= seen
