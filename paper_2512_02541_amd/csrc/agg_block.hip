@@ -561,7 +561,7 @@ hipError_t launch_linear(const void* A, const LinearOuts& outs, const void* R, i
   (void)hipGetLastError();
   const uint16_t* a = (const uint16_t*)A;
   const uint16_t* r = (const uint16_t*)R;
-  const LinearPlan plan = plan_linear(rows, N, K, outs.count);
+  const LinearPlan plan = plan_linear(rows, N, K, outs.count, r != nullptr);
   if (plan.split == 0) return launch_linear_edge(plan.edge, a, outs, r, rows, N, K, st);
   const hipError_t e = launch_linear_edge(kLargeEdge, a, outs, r, plan.split, N, K, st);
   if (e != hipSuccess) return e;

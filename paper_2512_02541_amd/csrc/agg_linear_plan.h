@@ -21,50 +21,66 @@ static inline int64_t few_tiles(int64_t rows, int N, int count) {
   return (rows + kFewEdge - 1) / kFewEdge * (N / kFewEdge) * count;
 }
 
-// Times of a launch in microseconds, from what a round of tiles took at K = 1024: 256-wide tiles 33,
-// one to a CU; 128-wide ones 20.6 two to a CU and 14 alone, 7 where a CU's last one runs alone behind
-// others.  They are taken to follow K, which stores and starts do not; at K = 128 to 4096 and 261 to
-// 137 400 rows (184 launches) the choice below took 0.85 to 1.03 of the better single size, once 1.07
-// (K = 512, 21 984 rows, three matrices: 46.3 against 43.4 us with small tiles alone).
-static inline double linear_time(int64_t rows, int edge, int N, int K, int count) {
-  const int64_t tiles = (rows + edge - 1) / edge * ((N + edge - 1) / edge) * count;
-  const int64_t mine = (tiles + kGemmXcds - 1) / kGemmXcds;  // of one XCD, which has 32 CUs
+// Time of one launch for `count` weight matrices [N, K], in microseconds.  A launch goes by rounds: a
+// CU runs one 256-wide tile or two of the others at a time, and an XCD has 32 CUs.  What a round costs has
+// a part that follows K (the steps) and one that does not (the stores, the residual's loads), and a round of at
+// most one small tile per CU is cheaper than a full one.
+//
+// The constants are fitted to 5 137 sizes timed with every choice of tiles, on three boxes, with what
+// surrounds a projection in a block: its input has just been written, the residual a while ago.  N = K = 64 to
+// 4096 in 19 widths, one matrix with the residual and three without, up to 300 000 rows.  Nine launches in ten
+// take 0.73 to 1.20 (tiles of 128) and 0.90 to 1.13 (of 256) of the time given here.
+static inline double linear_time(int64_t rows, int edge, int N, int K, int count, bool residual) {
+  const int64_t across = (N + edge - 1) / edge;
+  const int64_t tiles = (rows + edge - 1) / edge * across * count;
+  const int64_t mine = (tiles + kGemmXcds - 1) / kGemmXcds;  // of one XCD
+  const int64_t at_once = edge == kLargeEdge ? 32 : 64;
+  const int64_t full = mine / at_once, last = mine % at_once;
+  const double part = (double)last / at_once, rounds = full + part;
   const double k = K / 1024.0;
-  if (edge == kLargeEdge) return k * 33.0 * ((mine + 31) / 32);
-  const int64_t full = mine / 64, rest = mine % 64;
-  return k * (20.6 * full + (rest == 0 ? 0.0 : rest > 32 ? 20.6 : full ? 7.0 : 14.0));
+  if (edge == kLargeEdge) {
+    // channels past the end of a tile are not stored
+    const double stored = rounds * N / (double)(across * edge);
+    return 2.7 + (full + (last > 0)) * (0.6 + 24.6 * k) + stored * (residual ? 9.1 : 3.9);
+  }
+  const bool half = last > 0 && last <= 32;  // at most one tile per CU in the last round
+  const int64_t whole = full + (last > 32);
+  if (edge == kFewEdge) return 2.0 + whole * (1.5 + 6.0 * k) + half * (0.7 + 4.4 * k);
+  // Beyond what the last cache level holds, every 128-wide column of tiles reads the rows again.
+  const bool far = 2.0 * rows * (K + (count + residual) * (double)N) > 300e6;
+  return 2.5 + rounds * (1.4 + (residual ? 1.7 : 0.0) + (far ? 1.1 : 0.0)) +
+         k * (full * 17.3 + part * 5.3 + (last > 32 ? 11.7 : !half ? 0.0 : full ? 6.0 : 10.7));
 }
 
 // The plan for `count` weight matrices [N, K] applied to the same rows.
-static inline LinearPlan plan_linear(int64_t rows, int N, int K, int count) {
-  // Up to two 64-wide tiles per CU.  Tiles of 128 / of 64, us, by the number of the latter at C = 1024: 144
-  // 13.3 / 6.8; 288 13.3 / 9.7; 352 13.2 / 10.2; 432 13.7 / 10.9; beyond the line 688 14.1 / 16.7; 864 14.8 / 17.8.
-  // C = 1280: 260 15.5 / 10.8; 780 17.0 / 20.7.  C = 512: 216 8.7 / 5.7; 344 8.8 / 7.7; 1032 12.9 / 14.9.
+static inline LinearPlan plan_linear(int64_t rows, int N, int K, int count, bool residual) {
+  // Up to two 64-wide tiles per CU: the best choice, or within 1 % of it, at all of 957 sizes.  Tiles of 128 / of
+  // 64, us, by the number of the latter at C = 1024, launches back to back: 144 13.3 / 6.8; 288 13.3 / 9.7; 432 13.7 /
+  // 10.9; beyond the line 688 14.1 / 16.7; 864 14.8 / 17.8.  (Exceptions there: launches that would just begin their
+  // second half round of tiles of 128, 1065 rows of 1280 channels, three matrices, 22.5 / 19.7; 398 of 3072 49.6 / 39.9.)
   if (few_tiles(rows, N, count) <= 2 * kGemmCus) return {0, kFewEdge};
-  // Large tiles move half the bytes per product, small ones fill the chip and its last round: the
-  // rows of whole rounds of large tiles go to them and the others to small tiles, if that is at
-  // least 6 % ahead of large tiles alone and 3 % of small ones (a second launch costs 4 us).  Measured for the Q/K/V and
-  // the output projection at C = 1024, large / small / chosen, us:
-  // 5 496 rows 58 + 32 / 46 + 20 / 45 + 21; 10 992 rows 90 + 35 / 85 + 32 / 82 + 31; 32 976 rows
-  // 232 + 110 / 270 + 104 / 229 + 105; 137 400 rows 817 + 325 / 1022 + 374 / large.
+  // Large tiles move half the bytes per product, small ones fill the chip and its last round; or the rows of
+  // whole rounds of large tiles go to them and the others to small ones, or to tiles of 64 where these are few
+  // enough, by a second launch, which has to be 2 % ahead.  At the 5 137 sizes this took 1.003 of the best choice on
+  // average; 1.6 % are more than 6 % behind it, the worst 1.15 (23 983 rows of 768 channels, 42.0 us in two
+  // launches, 36.5 in tiles of 128).  (Times that only followed K, and a second launch 6 % ahead, took 1.009, 5 % of
+  // the sizes over 6 %: 1 480 rows of 4096 channels 176 us in tiles of 128, 140 in two launches.)  At C = 1024, tiles
+  // of 256 / of 128 / two launches, us: Q/K/V 5 651 rows 52 / 39 / 36; 21 960 135 / 141 / 119; 92 600 488 / 625 / 499;
+  // output 5 651 rows 29 / 16; 21 960 64 / 57 / 60; 103 206 240 / 264 / 236.
   const int64_t per_m = (int64_t)((N + 255) / 256) * count;
   const int64_t gm = (rows + 255) / 256;
   const int64_t whole = gm * per_m / kGemmCus * kGemmCus / per_m;  // token tiles that fill whole rounds
   const int64_t split = whole * 256 < rows ? whole * 256 : 0;
-  const double large = linear_time(rows, kLargeEdge, N, K, count);
-  const double small = linear_time(rows, kSmallEdge, N, K, count);
-  // The others take tiles of 64 where these are few enough: 7.5 us up to one per CU, 11 up to two, where a
-  // single round of small tiles takes 14 to 20.  Whole block, others in small tiles / in tiles of 64 (and
-  // then also where that makes two launches the better choice): 16 frames of 37x37, 239 others, 731.5 /
-  // 722.3; per-frame, 8 frames 188.5 / 181.3; 96 frames, 832, 1879 / 1864; 42 frames of 28x37 622 / 607;
-  // 167 frames of 16x16, 12 heads, 364 / 353.
-  const int64_t few_rest = few_tiles(rows - split, N, count);
-  const double rest_time = few_rest > 2 * kGemmCus ? linear_time(rows - split, kSmallEdge, N, K, count)
-                                                   : K / 1024.0 * (few_rest > kGemmCus ? 11.0 : 7.5);
-  const double both = split ? linear_time(split, kLargeEdge, N, K, count) + rest_time + 4.0 : large;
-  if (small < 0.97 * large && small <= 1.03 * both) return {0, kSmallEdge};
-  if (both >= 0.94 * large) return {0, kLargeEdge};
-  return {split, few_rest <= 2 * kGemmCus ? kFewEdge : kSmallEdge};
+  const double large = linear_time(rows, kLargeEdge, N, K, count, residual);
+  const double small = linear_time(rows, kSmallEdge, N, K, count, residual);
+  const double one = small < large ? small : large;
+  if (split) {
+    const int rest = few_tiles(rows - split, N, count) <= 2 * kGemmCus ? kFewEdge : kSmallEdge;
+    const double two = linear_time(split, kLargeEdge, N, K, count, residual) +
+                       linear_time(rows - split, rest, N, K, count, residual);
+    if (1.02 * two < one) return {split, rest};
+  }
+  return {0, small < large ? kSmallEdge : kLargeEdge};
 }
 
 }  // namespace agg

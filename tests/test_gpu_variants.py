@@ -84,17 +84,18 @@ PROJECTIONS = {
     (1, 3): ("64", "64"), (1, 129): ("64", "64"),
     (1, 30000): ("128", "64"),
     (3, 999): ("64", "64"),
-    (4, 66048): ("256+64", "128"),      # every tile of 128 and 256 whole
+    (4, 66048): ("128", "128"),         # every tile whole
     (5, 261): ("64", "64"),
     (16, 21999): ("256+64", "256+128"),
-    (16, 34353): ("256", "256+64"),
-    (33, 30000): ("256", "256+128"),    # 2112 channels: the last large tile of every matrix is a quarter full
+    (16, 34353): ("256+128", "256+64"),
+    (33, 30000): ("256+128", "256+128"),  # 2112 channels: the last large tile of every matrix is a quarter full
     (1, 33000): ("128", "128"),         # one k step, at most one tile per workgroup with the residual
     (1, 99999): ("128", "128"),         # ... and several
     (2, 69999): ("128", "128"),         # two k steps, several tiles per workgroup
     (3, 12000): ("128", "128"),         # 192 channels: the last tile of every matrix is half empty
-    (3, 49998): ("256", "256"),         # three k steps, and a quarter of every large tile empty
+    (3, 64998): ("256", "256"),         # three k steps, and a quarter of every large tile empty
     (5, 45000): ("128", "128"),         # 320 channels, several tiles per workgroup
+    (8, 65286): ("256", "256"),         # tiles of 256, whole but for the last tokens, several per workgroup
 }
 
 
