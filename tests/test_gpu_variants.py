@@ -141,6 +141,32 @@ def test_projection_few_tokens(H, rows):
     test_projection_tiles(H, rows)
 
 
+# (heads, rows) -> tiles, as above: calls whose rows are computed again, 66 at a time, in tiles of 64
+SAME_BITS = {
+    (2, 16386): ("128", "128"), (5, 7002): ("128", "128"), (16, 3000): ("128", "128"),
+    (3, 64998): ("256", "256"), (16, 21999): ("256+64", "256+128"), (16, 34353): ("256+128", "256+64"),
+}
+
+
+@pytest.mark.parametrize("H,rows", SAME_BITS)
+def test_projection_bits_do_not_depend_on_the_tiles(H, rows):
+    """Every tile size adds a channel's products in the same order.  Frames of three tokens attend to
+    nothing else, so a call with some of them gives those rows' bits of the whole call: the first ones, those on
+    both sides of the end of whole rounds of tiles of 256, and the last."""
+    C, L, few = 64 * H, 3, 66
+    wts = inputs.block_weights(C, seed=rows + H, device="cuda")
+    x = inputs.block_input(1, rows, C, seed=rows + H, device="cuda")
+
+    def block(x):
+        shape = agg.make_shape(1, x.shape[1] // L, 1, L, 0, H, 64, 1, 1, 0)
+        return harness.block_forward(shape, agg.AGG_BLOCK_FRAME, wts, x)[0].view(torch.int16)
+
+    y = block(x)
+    for at in {0, rows - few} | {end // L * L - 33 for end in (16384, 21760, 32768, rows // 256 * 256)}:
+        if at <= rows - few:
+            assert torch.equal(block(x[:, at:at + few].contiguous()), y[:, at:at + few]), at
+
+
 @pytest.mark.parametrize("H", [1, 3, 16, 33])
 @pytest.mark.parametrize("B,nq", [(1, 1024), (2, 1026), (1, 70000)])
 def test_mean_split_by_heads(H, B, nq):

@@ -161,6 +161,9 @@ def test_projection_cases_reach_their_kernels(tiles):
         for steps in (1, 2, 3, 5):
             assert (64, residual, steps) in seen and (128, residual, steps) in seen
         assert (64, residual, 4) in seen and (256, residual, 3) in seen
+    for (heads, rows), want in variants.SAME_BITS.items():
+        got = tiles([(r, 64 * heads, count) for r in (rows, 66) for count in (3, 1)])
+        assert tuple(_route(*g) for g in got) == want + ("64", "64"), (heads, rows, got)
     assert {("behind 256", edge, residual) for edge in (64, 128) for residual in (0, 1)} <= seen
 
 
