@@ -714,7 +714,7 @@ __device__ __forceinline__ bool attend(const AttnArgs& p, uint16_t* tiles, uint3
   const Geom& g = p.g;
   // The general path starts from an opaque thread number, so that the addresses it has in common
   // with a fast pass ahead of it in the same kernel are worked out again: held across the fast
-  // key loop they spilled (up to 33 registers).
+  // key loop they spilled (sga_attn_kernel).
   int thread = threadIdx.x;
   if (kGen) asm volatile("" : "+v"(thread));
   const int group = kMode != kAlone ? __builtin_amdgcn_readfirstlane(thread / kAttnThreads) : 0;
@@ -761,8 +761,8 @@ __device__ __forceinline__ bool attend(const AttnArgs& p, uint16_t* tiles, uint3
   // caller's list: membership comes from a bitmap, the dropped count from device memory
   const int64_t n_drop = p.nd_dev ? (int64_t)p.nd_dev[b] : g.n_dropped;
   // ordinary and per-frame attention have no extras; where that is known at compile time the fast
-  // path's code is a third shorter (the general path's would spill: 353 registers instead of 16 in
-  // the second launch, 149 to 192 instead of none where rows are redone in place)
+  // path's code is a third shorter (the general path's would spill: 363 to 532 registers instead of 9
+  // or 10 in the second launch, 64 to 271 instead of none where rows are redone in place)
   constexpr bool kExtras = kSrc != kSrcRows || kGen;
   const bool takes = kExtras && !(kSplit && group);
   const bool use_mean = takes && (p.flags & AGG_MEAN) && n_drop > 0;
@@ -990,7 +990,8 @@ __device__ __forceinline__ bool attend(const AttnArgs& p, uint16_t* tiles, uint3
   if (kGen) __syncthreads();
   if (group) return true;
   // (The thread number is made opaque here, so that this part's lane numbers and addresses are worked
-  // out again: held across the key loop they spilled two registers in the narrow index-driven kernels.)
+  // out again: held across the key loop they take 6 to 14 registers more, and the narrow index-driven
+  // kernels have none left.)
   int here = tid;
   asm volatile("" : "+v"(here));
   const int elane = here & 63, ec = here & 15, eG = elane >> 4;
@@ -1127,9 +1128,8 @@ constexpr int tail_blocks(int tail_q) { return tail_q == 192 ? 3 : 2; }
 // leaving the mark for a second launch.  At that width the general path needs no more registers
 // than the fast one, provided that nothing is held for it meanwhile: it starts from an opaque
 // thread number (attend) and reads the kernel's arguments again.  So no instance spills, which a
-// build test checks, and each uses within 13 registers what it uses without kRedo.  Sharing both
-// with the fast path spilled 14 registers (compacted), 32 (rows) and 33 (indexed) at full width,
-// some of them in every workgroup's epilogue.
+// build test checks, and each uses within 2 registers what it uses without kRedo (234 to 248).  Sharing
+// both with the fast path spills 4 registers (compacted), 14 (rows) and 25 (indexed) at full width.
 template <int kSrc, int kTailQ, bool kRedo>
 __global__ __launch_bounds__(kAttnThreads, kBlocksPerCu) void sga_attn_kernel(AttnArgs p) {
   __shared__ __align__(16) uint16_t tiles[kTileLds];
