@@ -447,8 +447,10 @@ struct TileCopier {
 };
 
 // Query tile of product i: 0 .. kJ-1, then back, so that consecutive products always have an operand
-// in common.  What toggles least takes least power, and the clock follows power here (layer of 100
-// frames 29.10 ms in plain order, 29.02 in this one; ordinary attention, 24 frames, 1474 / 1469 us).
+// in common.  Measured pass by pass against plain order on two boxes: layers of 100 and 800 frames take 0.1 to
+// 0.3 % less (29.05 ms instead of 29.13), calls under 6 ms the same.  With the row of ones (pv_unit) it is 0.8 to
+// 1.0 %; of 0.9 % under the counters 0.5 +- 0.2 were cycles and 0.4 +- 0.2 the clock, so less power is a part of it
+// at most.
 template <int kJ>
 constexpr int there_and_back(int i) {
   return (i / kJ) % 2 ? kJ - 1 - i % kJ : i % kJ;
@@ -479,8 +481,8 @@ __device__ __forceinline__ void score_unit(const Wave<kQB, kJ>& w, int tq, f32x4
 // O^T += V^T P^T for the unit whose probabilities are in w.P.  Fast path: the row sums are one
 // more product, a row of ones and fifteen of zeros against P^T: row 0 of that 16 x 16 result, in
 // the lanes G = 0, is the sum of the unit's 32 probabilities of a query, and the vector ALU adds
-// nothing.  (Sixteen rows of ones leave the sum in every lane but take more power: the layer of 100
-// frames 29.24 ms instead of 29.10, ordinary attention, 24 frames, 1483 us instead of 1474.)
+// nothing.  (Sixteen rows of ones leave the sum in every lane but take 0.7 % longer: the layer of 100
+// frames 29.25 ms instead of 29.05, ordinary attention, 24 frames, 1448 us instead of 1440; 0.3 to 0.7 % elsewhere.)
 template <bool kGen, int kQB, int kJ>
 __device__ __forceinline__ void pv_unit(Wave<kQB, kJ>& w, int pq) {
 #pragma unroll
