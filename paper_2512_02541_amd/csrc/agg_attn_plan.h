@@ -28,16 +28,19 @@ struct TilePlan {
 // A workgroup's whole key loop is one piece of work, so a launch of a few rounds loses up to a
 // round to its last, partly filled one, and a short sequence pays for up to 255 queries that do
 // not exist.  Narrow workgroups (192 or 128 queries) lose less there; they are not free, because
-// every K/V fragment then feeds fewer products.  Measured over 121 key tiles with 16 pairs, in
-// units of what two full-width workgroups on one CU take (201 us): a pair of 192 0.79, of 128 0.56;
-// one alone on its CU 0.53 (256 queries), 0.45 (192), 0.36 (128).  The plan takes the narrow
+// every K/V fragment then feeds fewer products.  Measured over 122 compacted key tiles with 16 pairs, in
+// units of what two full-width workgroups on one CU take (201 us): a pair of 192 0.79, of 128 0.58;
+// one alone on its CU 0.55 (256 queries), 0.44 (192), 0.34 (128); over 73 tiles, and with 12 pairs, the same within
+// 0.01.  Rows in place 0.80, 0.60; 0.58, 0.48, 0.37; through the index list 0.84, 0.63; 0.55, 0.47, 0.37.  The costs
+// below are those of a prologue that has since become shorter; the compacted figures in their place would
+// change one plan in ninety, by less than 3 % as the model sees it.  The plan takes the narrow
 // tail that the cost model below puts at least 1.5 % ahead of full-width workgroups alone.
-// Measured with it: 10 frames of 37x37 patches, 16 heads, 367 us instead of 401 (attention
-// alone); two frames of 16x16 patches 27.6 instead of 33.3 (the whole layer).  The model knows
+// Measured with it, attention alone: 10 frames of 37x37 patches, 16 heads, 345 us instead of 373; 24 frames of
+// 28x37, 12 heads, ordinary attention, 1452 instead of 1503.  The model knows
 // neither the key source nor the number of keys: over 120 random launches for which it takes narrow
-// workgroups (all three sources, 10 to 670 key tiles, 4 to 32 heads, 1 to 73 frames) they took 0.69 to
-// 1.03 of full-width ones alone, half of them under 0.91; the worst are 53 frames of 16x16 through
-// the index list with 20 heads, 474 / 462 us, and per-frame attention, 16 frames of 28x37, 79 / 77.
+// workgroups (all three sources, 1 to 408 key tiles, 4 to 32 heads, 1 to 70 frames) they took 0.70 to
+// 1.03 of full-width ones alone, half of them under 0.91; the worst are 10 frames of 37x37 with 20 heads, 484 / 471 us,
+// and 53 frames of 16x16 through the index list with 20 heads, 259 / 252.
 struct TileCost {
   int queries;
   double paired, alone;  // on a CU that holds two workgroups / this one only
@@ -74,17 +77,18 @@ static inline TilePlan plan_tiles(int64_t NQ, int npairs, int64_t key_tiles) {
   TilePlan best = {(int)((NQ + kQTile - 1) / kQTile), 0, 0, 0, 0};
   // At most one narrow workgroup per CU: eight wavefronts that share the keys give each SIMD two to
   // alternate between.  The call, us, four / eight wavefronts: 2 frames of 37x37 with 8 heads, every
-  // token a key (43 key tiles), 30.2 / 25.0; through the index list 42.3 / 35.2; one frame of 37x37
-  // with 16 heads (22 tiles) 18.7 / 17.6.  One key tile cannot be shared.
+  // token a key (43 key tiles), 28.2 / 24.5; through the index list 31.7 / 28.0; one frame of 37x37
+  // with 16 heads (22 tiles) 16.6 / 15.1.  With few tiles the eight can be behind: 2 frames of 16x16, 6 compacted
+  // tiles, 8.9 / 9.4.  One key tile cannot be shared.
   if (key_tiles >= 2 && npairs <= kCus && npairs * ((NQ + 127) / 128) <= kCus)
     return {0, (int)((NQ + 127) / 128), 128, 1, 1};
   if (npairs * NQ > INT32_MAX) return best;  // far past the sizes at which a tail matters
   // With at least a pair per CU the rounds are many, and what is left to gain are the queries
   // that do not exist; the tails then follow their pair's other tiles, whose keys they share.
-  // Per-frame attention, 90 frames of 37x37 patches: 710 us instead of 728.  Under eight key tiles they
+  // Per-frame attention, 90 frames of 37x37 patches: 662 us instead of 682.  Under eight key tiles they
   // are left out: while such launches had a second one behind them, 50 frames of 16x16 took 51.0 us
-  // with them and 50.2 without.  (Now that they redo rows in place it is 42.6 and 43.5; 300 frames of
-  // 5x10 37.2 and 49.1.)
+  // with them and 50.2 without.  (Now that they redo rows in place it is 39.9 and 40.4; 300 frames of
+  // 5x10 37.6 and 50.0.)
   const bool by_pair = npairs >= kCus;
   if (by_pair && key_tiles < 8) return best;
   double least = by_pair ? (double)best.n_full : launch_time(npairs * (int64_t)best.n_full, 0, kFullCost);
@@ -109,24 +113,24 @@ static inline TilePlan plan_tiles(int64_t NQ, int npairs, int64_t key_tiles) {
 
 // Whether a launch that is not split redoes rows itself, without a second launch.
 //
-// An idle second launch is 1 to 18 % of a call with few key tiles, and where one query needs the
+// An idle second launch is 1 to 17 % of a call with few key tiles, and where one query needs the
 // general path the others no longer wait for it; with long key loops the idle launch is lost in
 // them, and there redoing everything 128 queries at a time, which reads the keys twice, costs more.
 // Attention alone, us, second launch / redo in place, by the width of the last workgroups:
-//   full  rows, per-frame, 300 frames of 5x10, 1 tile 57.4 / 48.7;  50 frames of 16x16, 5 tiles 47.7 / 43.4;
-//         5 frames of 37x37, 22 tiles 43.1 / 41.0;  ordinary, 5 frames, 108 tiles 170.0 / 167.9
-//         compacted, 30 frames of 16x16, 3 tiles 28.3 / 26.3;  12 frames, 16 tiles 26.7 / 24.9;  3 frames of
-//         37x37, 12 heads, 44 tiles 51.0 / 49.0;  30 frames, 12 heads, 101 tiles 670 / 656
-//         indexed, 12 frames of 16x16, 16 tiles 27.5 / 26.0;  5 frames of 37x37, 45 tiles 88.1 / 86.2
-//   192   compacted, 20 frames of 16x16, 3 tiles 21.9 / 19.8;  2 frames of 37x37, 33 tiles 34.1 / 32.5;
-//         10 frames, 122 tiles 353 / 350;  indexed, 10 frames 379 / 376;  rows, 2 frames, 43 tiles 37.8 / 35.7
-//         (beyond the line: compacted, 12 frames, 133 tiles 488.5 / 485.0;  20 frames, 222 tiles 1254 / 1252)
-//   128   compacted, 9 frames, 1 tile 43.5 / 40.9;  3 frames, 44 tiles 55.6 / 53.7;
-//         rows, per-frame, 90 frames, 22 tiles 667 / 665;  300 frames of 24x24, 10 tiles 564 / 541
-// One query out of range / every workgroup: compacted, 10 frames of 37x37 573 / 351 and 512 / 596, the
-// largest loss; indexed, 8 frames of 16x16, 20 heads 33.2 / 36.1 and 32.7 / 36.5; rows, ordinary, 5 frames
-// 373 / 231 and 284 / 288; per-frame, 90 frames 737 / 654 and 1629 / 1515; 50 frames of 16x16 64.6 / 43.5
-// and 118.8 / 102.5.
+//   full  rows, per-frame, 300 frames of 5x10, 1 tile 58.2 / 49.7;  50 frames of 16x16, 5 tiles 43.6 / 40.0;
+//         5 frames of 37x37, 22 tiles 43.0 / 41.1;  ordinary, 5 frames, 108 tiles 168.5 / 166.5
+//         compacted, 30 frames of 16x16, 3 tiles 22.5 / 20.6;  12 frames, 16 tiles 24.0 / 22.2;  3 frames of
+//         37x37, 12 heads, 44 tiles 45.0 / 43.1;  30 frames, 12 heads, 101 tiles 639 / 633
+//         indexed, 12 frames of 16x16, 16 tiles 24.7 / 23.0;  5 frames of 37x37, 45 tiles 81.3 / 79.3
+//   192   compacted, 20 frames of 16x16, 3 tiles 18.8 / 16.5;  2 frames of 37x37, 33 tiles 30.7 / 28.7;
+//         10 frames, 122 tiles 348 / 344;  indexed, 10 frames 372 / 369;  rows, 2 frames, 43 tiles 36.9 / 35.0
+//         (beyond the line: compacted, 12 frames, 133 tiles 460 / 456;  20 frames, 222 tiles 1185 / 1183)
+//   128   compacted, 9 frames, 1 tile 29.0 / 26.1;  3 frames, 44 tiles 54.3 / 52.2;
+//         rows, per-frame, 90 frames, 22 tiles 669 / 662;  300 frames of 24x24, 10 tiles 558 / 540
+// One token out of range (a workgroup of every head) / every workgroup: compacted, 10 frames of 37x37 584 / 399 and
+// 535 / 639, the largest loss; indexed, 8 frames of 16x16, 20 heads 40.4 / 44.0 and 41.7 / 48.4; rows, ordinary, 5 frames
+// 340 / 230 and 281 / 290; per-frame, 90 frames 704 / 666 and 1533 / 1543; 50 frames of 16x16 56.4 / 41.0
+// and 101.9 / 94.1.
 static inline bool redo_in_place(int64_t key_tiles) { return key_tiles < 128; }
 
 }  // namespace agg
