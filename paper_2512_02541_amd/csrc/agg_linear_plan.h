@@ -61,24 +61,27 @@ static inline LinearPlan plan_linear(int64_t rows, int N, int K, int count, bool
   if (few_tiles(rows, N, count) <= 2 * kGemmCus) return {0, kFewEdge};
   // Large tiles move half the bytes per product, small ones fill the chip and its last round; or the rows of
   // whole rounds of large tiles go to them and the others to small ones, or to tiles of 64 where these are few
-  // enough, by a second launch, which has to be 2 % ahead.  At the 5 137 sizes this took 1.003 of the best choice on
-  // average; 1.6 % are more than 6 % behind it, the worst 1.15 (23 983 rows of 768 channels, 42.0 us in two
-  // launches, 36.5 in tiles of 128).  (Times that only followed K, and a second launch 6 % ahead, took 1.009, 5 % of
-  // the sizes over 6 %: 1 480 rows of 4096 channels 176 us in tiles of 128, 140 in two launches.)  At C = 1024, tiles
-  // of 256 / of 128 / two launches, us: Q/K/V 5 651 rows 52 / 39 / 36; 21 960 135 / 141 / 119; 92 600 488 / 625 / 499;
-  // output 5 651 rows 29 / 16; 21 960 64 / 57 / 60; 103 206 240 / 264 / 236.
+  // enough, by a second launch.  At the 5 137 sizes, where a second launch was taken when 2 % ahead, the choice was
+  // 1.003 of the best one on average and 1.15 at worst (23 983 rows of 768 channels, 42.0 us in two launches, 36.5 in
+  // tiles of 128); times that only followed K, 6 % ahead, gave 1.009.  Whole blocks gain less by a second launch than
+  // the projections' own times say (idle CUs leave the others more power, which may be why).  In per-frame blocks of
+  // 130 drawn sizes, each projection with and without its second launch, a predicted lead of 8 us over large
+  // tiles was mostly between a gain of 7 and a loss of 9, one of 16 us and more a gain of 4 to 20; 2 % ahead took 1.0012 of the best choice (11 220 rows of
+  // 512 channels 68.6 us, 66.6 without; 51 678 of 1024 636 / 624; 59 337 of 768 558 / 548), the leads asked for
+  // here 1.0006.  At C = 1024, tiles of 256 / of 128 / two launches, us: Q/K/V 5 651 rows 52 / 39 / 36; 21 960 135 / 141 /
+  // 119; 92 600 488 / 625 / 499; output 5 651 rows 29 / 16; 21 960 64 / 57 / 60; 103 206 240 / 264 / 236 (within
+  // a block the same).
   const int64_t per_m = (int64_t)((N + 255) / 256) * count;
   const int64_t gm = (rows + 255) / 256;
   const int64_t whole = gm * per_m / kGemmCus * kGemmCus / per_m;  // token tiles that fill whole rounds
   const int64_t split = whole * 256 < rows ? whole * 256 : 0;
   const double large = linear_time(rows, kLargeEdge, N, K, count, residual);
   const double small = linear_time(rows, kSmallEdge, N, K, count, residual);
-  const double one = small < large ? small : large;
   if (split) {
     const int rest = few_tiles(rows - split, N, count) <= 2 * kGemmCus ? kFewEdge : kSmallEdge;
     const double two = linear_time(split, kLargeEdge, N, K, count, residual) +
                        linear_time(rows - split, rest, N, K, count, residual);
-    if (1.02 * two < one) return {split, rest};
+    if (two + (residual ? 5 : 2) < small && 1.02 * two + 5 < large) return {split, rest};
   }
   return {0, small < large ? kSmallEdge : kLargeEdge};
 }
