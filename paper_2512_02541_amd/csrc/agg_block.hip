@@ -131,7 +131,7 @@ __global__ __launch_bounds__(kLnThreads) void layernorm_kernel(const uint16_t* _
 // Measured at 137 400 rows, C = 1024 (us for Q/K/V and for the output projection): 1060 + 420
 // before (256 x 256 tiles through registers, one workgroup per tile); 1040 + 400 with 256 x 128
 // tiles, two to a CU, 32-wide k; 855 + 360 persistent with two 64 KiB stages; 817 + 325 as it is
-// (1.06 PFLOP/s); on a slower box 840 + 328, the output projection in two launches, where the library's products
+// (1.06 PFLOP/s); on other boxes 797 + 324 and 840 + 328, on the last of which the library's products
 // without residual take 786 + 272.  Without its copies it takes 610, without copies and stores 552, the products
 // alone 480; spreading a step's copies over its products, grouping token tiles, touching lines
 // ahead of the copies and streaming stores made it no faster or slower.
